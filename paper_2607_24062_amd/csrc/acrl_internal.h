@@ -21,15 +21,22 @@ hipError_t launch_fp8_encode(const float* x, int64_t n, int rounding, uint8_t* q
 hipError_t launch_quantize(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld, int scaling,
                            int rounding, uint8_t* q, void* scales, void* workspace, hipStream_t s);
 
+// Grid raster of a launch: blocks of block_t token tiles x block_s strips.
+struct Raster {
+  int n_tblocks, n_sblocks, n_blocks;
+  int block_t, block_s;
+  int grid;             // units, the blocks rounded up to a multiple of 8
+};
+Raster raster_blocks(int n_ttiles, int n_strips);
+
 struct ScorePlan {
-  int n_ttiles;         // token tiles of 256 rows
+  int tile_t;           // tokens per workgroup tile: 64, 128 or 256
+  int n_ttiles;         // token tiles of tile_t rows
+  int n_ptiles;         // packed token tiles of 256 rows
   int n_vtiles;         // vocabulary tiles of 256 rows
   int tiles_per_strip;  // vocabulary tiles per workgroup
   int n_strips;         // vocabulary strips (partial softmax states per row)
-  int n_tblocks;        // token-tile blocks of kBlockT tiles (grid rasterization)
-  int n_sblocks;        // strip blocks of kBlockS strips
-  int n_blocks_pad;     // n_tblocks * n_sblocks rounded up to a multiple of 8
-  int grid;             // workgroups launched (n_blocks_pad * kBlockT * kBlockS)
+  Raster raster;
   size_t ws_part_offset[2];  // byte offsets of the (M, S, U) partials of pi / mu
   size_t ws_logit_offset[2]; // byte offsets of the sampled-token logits of pi / mu
   size_t ws_pack_offset[4];  // byte offsets of the packed W, H (bf16) and Wq, Hq (e4m3)
@@ -43,8 +50,9 @@ struct ScorePlan {
   size_t ws_bytes;
 };
 // div_rows > 0 plans the full-vocabulary measures in passes of div_rows rows;
-// prepacked: W's and Wq's images come from the caller (no workspace for them).
-ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows = 0, bool prepacked = false);
+// prepacked: W's and Wq's images come from the caller (no workspace for them);
+// narrow: token tiles of 64 and 128 rows may be planned (scoring, sampling).
+ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows, bool prepacked, bool narrow);
 constexpr int64_t kDivergenceChunk = 16384;  // default rows per pass of the full-vocabulary measures
 // Caller-owned packed LM head (acrl_pack_weights): byte offsets of the W,
 // Wq and Wq-MX-scale images.

@@ -12,6 +12,7 @@
 //  * Workgroup tile: 256 vocabulary rows x 256 tokens, one workgroup per CU,
 //    4 waves of 128 x 128 (256 accumulators per lane) or 8 waves of 128 x 64
 //    (128 accumulators, two waves per SIMD), chosen per instantiation.
+//    Calls of few tokens take tiles of 64 or 128 tokens (plan_score).
 //    BF16: v_mfma_f32_32x32x16_bf16.  FP8: v_mfma_f32_32x32x64_f8f6f4.
 //    MXFP8: v_mfma_scale_f32_32x32x64_f8f6f4 with per-lane E8M0 block scales.
 //  * K is streamed in 64-byte chunks per row (32 bf16 or 64 fp8 values) from
@@ -58,20 +59,20 @@ enum Epilogue {
 };
 
 constexpr int kTileV = 256;            // vocabulary rows per workgroup tile
-constexpr int kTileT = 256;            // tokens per workgroup tile
+constexpr int kTileT = 256;            // rows per packed token tile; tokens per workgroup tile (narrow variants: 64, 128)
 constexpr int kChunk = 64;             // bytes of K per row per pipeline stage
-constexpr int kThreads = 256;          // 4 waves; score_kernel<..., 8> runs 8 (two per SIMD)
-constexpr int kStageBytes = (kTileV + kTileT) * kChunk;  // 32 KiB
 constexpr int kPackBlock = kTileV * kChunk;               // packed image of one (tile, chunk): 16 KiB
 constexpr float kInitMax = -1.0e30f;   // running max before any logit was seen
 // Grid rasterization: the 32 workgroups an XCD runs at the same time (one per
-// CU) form a block of kBlockT token tiles x kBlockS vocabulary strips, so
-// each H chunk is shared by 4 and each W chunk by 8 workgroups in that
-// XCD's L2 (8 x 4 measured a few percent faster than 4 x 8 at 4096 x
-// 151936).  Workgroups are dispatched to the 8 XCDs round-robin.
+// CU) form a block of block_t token tiles x block_s vocabulary strips, so
+// each H chunk is shared by block_s and each W chunk by block_t workgroups in
+// that XCD's L2.  With 8 or more token tiles the block is 8 x 4 (measured a
+// few percent faster than 4 x 8 at 4096 x 151936); with fewer it has just
+// those and more strips (raster_blocks).  Workgroups are dispatched to the 8
+// XCDs round-robin.
 constexpr int kXcds = 8;
 constexpr int kBlockT = 8;
-constexpr int kBlockS = 4;
+constexpr int kBlockUnits = 32;
 
 struct ScoreParams {
   const uint8_t* a;        // packed W (bf16) or Wq (e4m3): [n_vtiles][n_chunks][16 KiB]
@@ -84,6 +85,7 @@ struct ScoreParams {
   int n_strips;
   int n_ttiles;
   int n_tblocks;
+  int block_t, block_s;    // raster block: token tiles x strips
   const float* a_scale;    // FP8 per-row: [V]; per-tensor: [1]
   const float* b_scale;    // FP8 per-row: [n_rows]; per-tensor: [1]
   const uint8_t* a_mx;     // MX: packed E8M0 image of W's scales (pack_mx_kernel)
@@ -122,7 +124,8 @@ struct ScoreParams {
   // persistent grid: one claim counter per XCD (kQueueStride ints apart,
   // zero at launch) and the units in each XCD's queue
   int* queue;
-  int units_per_xcd;
+  int units_per_xcd;       // units of the XCD that has most
+  int n_blocks;            // raster blocks (block i belongs to XCD i % kXcds)
 };
 constexpr int kQueueStride = 16;  // 64 bytes between the XCDs' counters
 
@@ -274,17 +277,21 @@ __device__ __forceinline__ void wait_vmcnt() {
 // NS + 1 vocabulary tiles (a tile's scales arrive with its first chunk, up to
 // NS chunks before the previous tile's epilogue reads its own), so both keep
 // one operand stage less.
-template <int MODE>
+template <int MODE, int TT>
 struct Pipe {
-  static constexpr int kStages = (MODE == kMX || MODE == kFP8Row) ? 4 : 5;
+  static constexpr int kStageBytes = (kTileV + TT) * kChunk;  // 32 KiB at 256 tokens, 20 KiB at 64
+  // 160 KiB of LDS hold 5 stages of 32 KiB (4 beside the scales), 6 of 24 KiB
+  // or 8 of 20 KiB (7 beside the scales)
+  static constexpr bool kScales = MODE == kMX || MODE == kFP8Row;
+  static constexpr int kStages = TT == 256 ? (kScales ? 4 : 5) : TT == 128 ? 6 : (kScales ? 7 : 8);
   static constexpr int kScaleBytes = (MODE == kMX) ? (kTileV + kTileT) * 2 : 0;  // per stage
   static constexpr int kRowScaleSlots = kStages + 1;
   static constexpr int kRowScaleBytes = (MODE == kFP8Row) ? kRowScaleSlots * kTileV * 4 : 0;
-  // buffer -> LDS loads per chunk per wave: the two 16 KiB tile images spread
-  // over NW waves (1 KiB per load), plus one quarter of the MX scales (4
-  // bytes per lane)
+  // buffer -> LDS loads per chunk per wave: the two tile images spread over NW
+  // waves (1 KiB per load), plus one quarter of the MX scales (4 bytes per
+  // lane)
   template <int NW>
-  static constexpr int loads_per_chunk() { return 2 * (16 / NW) + (MODE == kMX ? 1 : 0); }
+  static constexpr int loads_per_chunk() { return (kTileV + TT) / (16 * NW) + (MODE == kMX ? 1 : 0); }
 };
 
 // NW = 4: one wave per SIMD, each wave 128 vocabulary rows x 128 tokens
@@ -292,33 +299,49 @@ struct Pipe {
 // per SIMD, each 128 x 64 (4 x 2 blocks, 128 accumulators): while one wave
 // waits at the chunk barrier or runs its softmax epilogue the other keeps
 // the SIMD's matrix core busy.
+// JT: token blocks of 32 per wave, so a workgroup tile has TT = 16 NW JT
+// tokens: 256 (JT = 16 / NW), or 128 / 64 for calls of few tokens, where the
+// W stream from HBM and not the matrix cores bounds the kernel and the
+// columns of a wider tile would be padding.  Every width gives a token's
+// lanes the same vocabulary rows in the same order, so the logits and the
+// strip states do not depend on it.
 // PERSIST: one workgroup per CU claims units from per-XCD queues (below);
 // otherwise one workgroup per unit.
-template <int MODE, int EPI, int NW, bool PERSIST>
+template <int MODE, int EPI, int NW, int JT, bool PERSIST>
 __global__ __attribute__((amdgpu_flat_work_group_size(NW * 64, NW * 64), amdgpu_waves_per_eu(NW / 4, NW / 4)))
 void score_kernel(ScoreParams p) {
   static_assert(NW == 4 || NW == 8, "4 or 8 waves");
-  constexpr int JT = 16 / NW;   // token blocks of 32 per wave
-  constexpr int TW = 32 * JT;   // tokens per wave
+  constexpr int TW = 32 * JT;        // tokens per wave
+  constexpr int TT = TW * (NW / 2);  // tokens per workgroup tile
+  static_assert(TT == 64 || TT == 128 || TT == 256, "token tile");
   constexpr bool SAMPLE = EPI == kEpiSample;
   constexpr bool DIV = EPI == kEpiSoftmaxDiv;
   constexpr bool SOFTMAX = EPI == kEpiSoftmax || EPI == kEpiSample || EPI == kEpiSoftmaxZ || DIV;
   static_assert(MODE == kBF16 || SOFTMAX, "the backward epilogues take bf16 operands");
   static_assert(!DIV || MODE == kBF16, "the measures are accumulated in pi's pass");
-  constexpr int NS = Pipe<MODE>::kStages;
+  static_assert(TT == kTileT || EPI == kEpiSoftmax || EPI == kEpiSample, "narrow token tiles score and sample only");
+  constexpr int NS = Pipe<MODE, TT>::kStages;
+  constexpr int kStageBytes = Pipe<MODE, TT>::kStageBytes;
+  // accumulators held in VGPRs (the MFMA's VGPR form): the 8-wave per-row FP8
+  // kernels and the 8-wave passes of the full-vocabulary measures (12 instead
+  // of 112 bytes spilled per lane in the persistent per-row scorer, mu 1.5-7 %
+  // faster, and 12 instead of 104 in pi's measures pass, the measures 6 ms
+  // cheaper at d = 4096; the plain 256-token BF16 and per-tensor FP8 scorers
+  // ran slower that way), and every narrow tile (at most 128 accumulators)
+  constexpr bool kAccV = ((MODE == kFP8Row || EPI == kEpiSoftmaxZ || DIV) && NW == 8) || TT < kTileT;
   // FP8 per-tensor / MX scorers start each tile's accumulators with an
   // inline-zero MFMA instead of clearing them after the epilogue (measured:
   // faster there; the BF16 and per-row FP8 kernels keep the clearing)
   constexpr bool kZeroStart = SOFTMAX && (MODE == kFP8Tensor || MODE == kMX);
-  constexpr int SB = Pipe<MODE>::kScaleBytes;
-  constexpr int LPC = Pipe<MODE>::template loads_per_chunk<NW>();
-  constexpr int RSB = Pipe<MODE>::kRowScaleBytes;
+  constexpr int SB = Pipe<MODE, TT>::kScaleBytes;
+  constexpr int LPC = Pipe<MODE, TT>::template loads_per_chunk<NW>();
+  constexpr int RSB = Pipe<MODE, TT>::kRowScaleBytes;
   static_assert(MODE != kMX || NW == 4, "the MX scale stream is spread over 4 waves");
   __shared__ __attribute__((aligned(1024))) uint8_t lds[NS * (kStageBytes + SB) + RSB];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wv = wave & 1;   // which 128-row half of the vocabulary tile
-  const int wt = wave >> 1;  // which 128-token half of the token tile
+  const int wt = wave >> 1;  // which TW tokens of the token tile
   const int r32 = lane & 31, g = lane >> 5;
   const int sw = (lane >> 2) & 3;  // swizzle of this lane's fragment row (see below)
 
@@ -327,7 +350,7 @@ void score_kernel(ScoreParams p) {
   auto unit = [&](int tt, int st) {
   if (tt >= p.n_ttiles || st >= p.n_strips) return;  // padding of the grid
   const int ttg = tt + p.tt_offset;  // token tile in the whole call
-  const int t0 = ttg * kTileT;
+  const int t0 = ttg * TT;
   const int vt_begin = st * p.tiles_per_strip;
   const int vt_end = min(vt_begin + p.tiles_per_strip, p.n_vtiles);
   const int n_iter = (vt_end - vt_begin) * p.n_chunks;
@@ -387,8 +410,9 @@ void score_kernel(ScoreParams p) {
     }
   }
 
-  // ---- global -> LDS.  A stage holds one 64-byte K chunk of all 256 + 256
-  // rows (W tile rows first).  Operands come packed (pack_kernel): the
+  // ---- global -> LDS.  A stage holds one 64-byte K chunk of all 256 + TT
+  // rows (W tile rows first; a narrow token tile is a contiguous part of its
+  // 256-row image).  Operands come packed (pack_kernel): the
   // 16 KiB image of each (256-row tile, chunk) pair is stored contiguously
   // exactly as the stage holds it, so a wave moves 4 KiB of contiguous
   // memory per tile with 4 buffer -> LDS loads of 1 KiB (lane l: bytes
@@ -399,12 +423,13 @@ void score_kernel(ScoreParams p) {
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t lane_off = (uint32_t)lane * 16;
   const uint32_t tile_bytes = (uint32_t)p.n_chunks * kPackBlock;  // packed bytes of one tile
-  const int b_rows = min(kTileT, p.n_rows - t0);  // valid rows of the token tile
-  const __amdgpu_buffer_rsrc_t rsrc_b = make_rsrc(p.b + (int64_t)ttg * tile_bytes, tile_bytes);
+  const int ptile = t0 / kTileT;                      // packed tile of the tokens
+  const uint32_t b_sub = (uint32_t)(t0 % kTileT);      // and their first row in it
+  const __amdgpu_buffer_rsrc_t rsrc_b = make_rsrc(p.b + (int64_t)ptile * tile_bytes, tile_bytes);
   auto stage_at = [&](int stg) { return lds + stg * kStageBytes; };
   auto scales_at = [&](int stg) { return lds + NS * kStageBytes + stg * SB; };
   auto rowscales_at = [&](int q) {  // FP8 per-row: weight-row scales of tile q
-    return reinterpret_cast<float*>(lds + NS * (kStageBytes + SB) + (q % Pipe<MODE>::kRowScaleSlots) * kTileV * 4);
+    return reinterpret_cast<float*>(lds + NS * (kStageBytes + SB) + (q % Pipe<MODE, TT>::kRowScaleSlots) * kTileV * 4);
   };
 
   auto issue_chunk = [&](int q, int kc, int stg) {  // chunk kc of the strip's tile q into stage stg
@@ -413,11 +438,13 @@ void score_kernel(ScoreParams p) {
     const __amdgpu_buffer_rsrc_t rsrc_a = make_rsrc(p.a + (int64_t)(vt_begin + q) * tile_bytes, tile_bytes);
     const uint32_t soff = (uint32_t)kc * kPackBlock + (uint32_t)wave_u * (kPackBlock / NW);
     uint8_t* la = stage_at(stg) + wave_u * (kPackBlock / NW);
-    uint8_t* lb = la + kTileV * kChunk;
+    constexpr int kBWave = TT * kChunk / NW;  // bytes of the token tile per wave
+    const uint32_t soff_b = (uint32_t)kc * kPackBlock + b_sub * kChunk + (uint32_t)wave_u * kBWave;
+    uint8_t* lb = stage_at(stg) + kTileV * kChunk + wave_u * kBWave;
 #pragma unroll
     for (int k = 0; k < 16 / NW; ++k) buffer_to_lds<16>(rsrc_a, lane_off, soff + k * 1024, la + k * 1024);
 #pragma unroll
-    for (int k = 0; k < 16 / NW; ++k) buffer_to_lds<16>(rsrc_b, lane_off, soff + k * 1024, lb + k * 1024);
+    for (int k = 0; k < kBWave / 1024; ++k) buffer_to_lds<16>(rsrc_b, lane_off, soff_b + k * 1024, lb + k * 1024);
     if constexpr (MODE == kFP8Row) {
       // with a tile's first chunk: its 256 weight-row scales (lane l of wave
       // w moves row 64w + l); they land long before the tile's epilogue
@@ -433,7 +460,7 @@ void score_kernel(ScoreParams p) {
       // contiguous bytes per wave in the packed scale images
       const uint32_t tmx = (uint32_t)kTileV * (uint32_t)p.mx_row_bytes;  // bytes of one tile's image
       const __amdgpu_buffer_rsrc_t rs = wave_u < 2 ? make_rsrc(p.a_mx + (int64_t)(vt_begin + q) * tmx, tmx)
-                                                   : make_rsrc(p.b_mx + (int64_t)ttg * tmx, tmx);
+                                                   : make_rsrc(p.b_mx + (int64_t)ptile * tmx, tmx);
       buffer_to_lds<4>(rs, (uint32_t)lane * 4u, (uint32_t)kc * 512u + (uint32_t)(wave_u & 1) * 256u,
                        scales_at(stg) + wave_u * 256);
     }
@@ -489,7 +516,11 @@ void score_kernel(ScoreParams p) {
     return *reinterpret_cast<const int*>(scales_at(stg) + ((wv * 2 + g) * 32 + r32) * 4);
   };
   auto read_sb = [&](int stg) -> int {
-    return *reinterpret_cast<const int*>(scales_at(stg) + 2 * kTileV + ((wt * 2 + g) * 32 + r32) * 4);
+    // (a narrow tile's blocks start at block b_sub / 32 + wt * JT of the
+    // 256-row image: that block's byte moves to byte 0)
+    const int blk = (int)(b_sub / 32) + wt * JT;
+    const int x = *reinterpret_cast<const int*>(scales_at(stg) + 2 * kTileV + (((blk >> 2) * 2 + g) * 32 + r32) * 4);
+    return JT == 4 ? x : (int)((unsigned)x >> (8 * (blk & 3)));
   };
   // zc: the accumulators start from zero (the first K step of a tile), so
   // the MFMA takes an inline zero instead of them and no clearing is needed
@@ -581,15 +612,7 @@ void score_kernel(ScoreParams p) {
           float v[16];
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
-            // (the 8-wave per-row FP8 kernels and the 8-wave passes of the
-            // full-vocabulary measures keep their accumulators in VGPRs, the
-            // MFMA's VGPR form: 12 instead of 112 bytes spilled per lane in
-            // the persistent per-row scorer, mu 1.5-7 % faster, and 12
-            // instead of 104 in pi's measures pass, the measures 6 ms
-            // cheaper at d = 4096; the plain BF16 and per-tensor FP8 scorers
-            // ran slower that way)
-            v[i] = ((MODE == kFP8Row || EPI == kEpiSoftmaxZ || DIV) && NW == 8) ? acc[b][j][i]
-                                                                                : acc_read(acc[b][j][i]);
+            v[i] = kAccV ? acc[b][j][i] : acc_read(acc[b][j][i]);
             if constexpr (MODE == kFP8Row) v[i] *= rs[i];
           }
           if constexpr (EPI == kEpiSoftmaxZ) {
@@ -1105,41 +1128,47 @@ void score_kernel(ScoreParams p) {
 
   // ---- which units this workgroup runs.  Unit i of XCD x is the i-th
   // workgroup that XCD would get from a grid of one workgroup per unit
-  // (workgroups go to the XCDs round robin): blocks of kBlockT token tiles x
-  // kBlockS strips, so that an XCD's concurrent units share W and H chunks
-  // in its L2.  Persistent: one workgroup per CU takes the next unit of its
-  // own XCD's queue, and once that is empty the next of the other XCDs'
-  // queues, so that XCDs that run faster take more units (a fixed share per
-  // XCD leaves the faster ones idle at the end).  Every claim is one atomic
-  // on the queue's counter; a workgroup exits once every queue is empty.
-  constexpr int per = kBlockT * kBlockS;
+  // (workgroups go to the XCDs round robin): blocks of block_t token tiles x
+  // block_s strips, so that an XCD's concurrent units share W and H chunks
+  // in its L2.  Persistent: one workgroup per CU; its first unit is the one
+  // its place in the grid gives, then it takes the next of its own XCD's
+  // queue, and once that is empty the next of the other XCDs' queues, so
+  // that XCDs that run faster take more units (a fixed share per XCD leaves
+  // the faster ones idle at the end).  Every claim is one atomic on the
+  // queue's counter; a workgroup exits once every queue is empty, and a grid
+  // that holds every unit makes no claim at all.
+  const int per = p.block_t * p.block_s;
   auto run_unit = [&](int x, int i) {
     const int blk = (i / per) * kXcds + x, k = i % per;
-    unit((blk % p.n_tblocks) * kBlockT + k / kBlockS, (blk / p.n_tblocks) * kBlockS + k % kBlockS);
+    unit((blk % p.n_tblocks) * p.block_t + k / p.block_s, (blk / p.n_tblocks) * p.block_s + k % p.block_s);
   };
   if constexpr (!PERSIST) {
     run_unit((int)(blockIdx.x % kXcds), (int)(blockIdx.x / kXcds));
   } else {
+    const int n_first = (int)(gridDim.x / kXcds);  // units per XCD that the grid itself takes (a multiple of 8 workgroups)
     // the XCD this workgroup runs on (XCC_ID hardware register, bits 3:0)
     const int xcc = (int)(__builtin_amdgcn_s_getreg((3 << 11) | 20) & (kXcds - 1));
     int* slot = reinterpret_cast<int*>(lds);  // the stages are free between units
+    int c = (int)(blockIdx.x % kXcds) * p.units_per_xcd + (int)(blockIdx.x / kXcds);
     for (;;) {
+      const int x = c / p.units_per_xcd;
+      run_unit(x, c - x * p.units_per_xcd);
+      if (n_first >= p.units_per_xcd) break;
+      __syncthreads();  // the unit's last LDS reads are done
       if (tid == 0) {
         int claim = -1;
         for (int a = 0; a < kXcds && claim < 0; ++a) {
-          const int x = (xcc + a) & (kXcds - 1);
-          const int t = atomicAdd(p.queue + kQueueStride * x, 1);
-          if (t < p.units_per_xcd) claim = x * p.units_per_xcd + t;
+          const int y = (xcc + a) & (kXcds - 1);
+          const int t = n_first + atomicAdd(p.queue + kQueueStride * y, 1);
+          // units of XCD y: its share of the raster blocks
+          if (t < (p.n_blocks + kXcds - 1 - y) / kXcds * per) claim = y * p.units_per_xcd + t;
         }
         *slot = claim;
       }
       __syncthreads();
-      const int c = *slot;
+      c = *slot;
       __syncthreads();  // every wave has its claim before the stages are written
       if (c < 0) break;
-      const int x = c / p.units_per_xcd;
-      run_unit(x, c - x * p.units_per_xcd);
-      __syncthreads();  // the unit's last LDS reads are done
     }
   }
 }
@@ -1181,21 +1210,32 @@ inline int device_cus() {
   return n;
 }
 
-template <int MODE, int EPI>
-void launch_score_kernel(unsigned grid, const ScoreParams& p, hipStream_t s) {
-  constexpr int NW = waves_for<MODE, EPI>();
+template <int MODE, int EPI, int NW, int JT>
+void launch_tile(unsigned grid, const ScoreParams& p, hipStream_t s) {
   constexpr bool kPersist = (EPI == kEpiSoftmax || EPI == kEpiSample || EPI == kEpiSoftmaxZ || EPI == kEpiSoftmaxDiv ||
                              EPI == kEpiStore) &&
                             !(MODE == kFP8Row && EPI == kEpiSoftmaxZ);
   if constexpr (kPersist) {
     ScoreParams q = p;
     q.units_per_xcd = (int)(grid / kXcds);
-    hipLaunchKernelGGL(clear_queue_kernel, dim3(1), dim3(kXcds), 0, s, q.queue);
-    const unsigned wgs = std::min<unsigned>(grid, (unsigned)device_cus());
-    hipLaunchKernelGGL((score_kernel<MODE, EPI, NW, true>), dim3(wgs), dim3(NW * 64), 0, s, q);
+    const unsigned wgs = std::min<unsigned>(grid, (unsigned)device_cus() / kXcds * kXcds);
+    if (wgs < grid) hipLaunchKernelGGL(clear_queue_kernel, dim3(1), dim3(kXcds), 0, s, q.queue);
+    hipLaunchKernelGGL((score_kernel<MODE, EPI, NW, JT, true>), dim3(wgs), dim3(NW * 64), 0, s, q);
   } else {
-    hipLaunchKernelGGL((score_kernel<MODE, EPI, NW, false>), dim3(grid), dim3(NW * 64), 0, s, p);
+    hipLaunchKernelGGL((score_kernel<MODE, EPI, NW, JT, false>), dim3(grid), dim3(NW * 64), 0, s, p);
   }
+}
+
+// tile_t: tokens per workgroup tile (plan_score); the narrow ones exist for
+// the scoring and sampling epilogues.
+template <int MODE, int EPI>
+void launch_score_kernel(unsigned grid, const ScoreParams& p, hipStream_t s, int tile_t = kTileT) {
+  constexpr int NW = waves_for<MODE, EPI>();
+  if constexpr (EPI == kEpiSoftmax || EPI == kEpiSample) {
+    if (tile_t == 64) return launch_tile<MODE, EPI, 4, 1>(grid, p, s);
+    if (tile_t == 128) return launch_tile<MODE, EPI, NW, 8 / NW>(grid, p, s);
+  }
+  launch_tile<MODE, EPI, NW, 16 / NW>(grid, p, s);
 }
 
 // Packed operand image read by score_kernel: for each 256-row tile and each
@@ -1293,24 +1333,60 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ p, i
     p[i] = 0.0f;
 }
 
-// lse of row r in log2 units (M + log2 S) from the strips' (M, S, U) states.
-__device__ __forceinline__ float merged_lse2(const float* part, int64_t plane, int n_strips, int n_rows, int r) {
-  float M = kInitMax, S = 0.f, U = 0.f;
-  for (int s = 0; s < n_strips; ++s) {
+// The strips' (M, S, U) states of a row, merged by kMergeGroups threads: thread
+// group g takes strips g, g + kMergeGroups, ...; first the rows' maximum over
+// all strips, then the sums relative to it, the groups' sums added in group
+// order.  A workgroup holds kMergeRows rows; all its threads call this (two
+// barriers) and all get the row's state.  Two passes of independent loads
+// instead of one chain of pairwise merges: the chain over 30-200 strips took
+// 34-60 us a call, whatever the number of rows (8-9 us now, at 64-1017 rows).
+constexpr int kMergeRows = 16, kMergeGroups = 16;
+constexpr int kMergeThreads = kMergeRows * kMergeGroups;
+struct MergeShared {
+  float m[kMergeGroups][kMergeRows], s[kMergeGroups][kMergeRows], u[kMergeGroups][kMergeRows];
+};
+__device__ __forceinline__ void merge_strips(const float* __restrict__ part, int64_t plane, int n_strips, int n_rows,
+                                             int r, int rl, int grp, MergeShared& sh, float& M, float& S, float& U) {
+  float mx = kInitMax;
+#pragma unroll 4
+  for (int s = grp; s < n_strips; s += kMergeGroups) mx = fmaxf(mx, part[(int64_t)s * n_rows + r]);
+  sh.m[grp][rl] = mx;
+  __syncthreads();
+  M = sh.m[0][rl];
+#pragma unroll
+  for (int k = 1; k < kMergeGroups; ++k) M = fmaxf(M, sh.m[k][rl]);
+  float s1 = 0.0f, u1 = 0.0f;
+#pragma unroll 4
+  for (int s = grp; s < n_strips; s += kMergeGroups) {
     const int64_t o = (int64_t)s * n_rows + r;
-    merge_state(M, S, U, part[o], part[plane + o], part[2 * plane + o]);
+    const float dM = part[o] - M, ss = part[plane + o], uu = part[2 * plane + o];
+    const float a = fast_exp2(dM);
+    s1 = fmaf(a, ss, s1);
+    u1 = fmaf(a, fmaf(dM, ss, uu), u1);
   }
-  return M + log2f(S);
+  sh.s[grp][rl] = s1;
+  sh.u[grp][rl] = u1;
+  __syncthreads();
+  S = sh.s[0][rl];
+  U = sh.u[0][rl];
+#pragma unroll
+  for (int k = 1; k < kMergeGroups; ++k) {
+    S += sh.s[k][rl];
+    U += sh.u[k][rl];
+  }
 }
 
 // mu's log-sum-exp (log2 units) of rows r0 .. r0 + rows - 1 for the pi pass
 // of the full-vocabulary measures; entries rows .. cap - 1 (token-tile
 // padding) get 0.
-__global__ __launch_bounds__(256) void lse2_kernel(const float* __restrict__ part, int n_strips, int n_rows, int r0,
-                                                   int rows, int cap, float* __restrict__ out) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= cap) return;
-  out[k] = k < rows ? merged_lse2(part, (int64_t)n_strips * n_rows, n_strips, n_rows, r0 + k) : 0.0f;
+__global__ __launch_bounds__(kMergeThreads) void lse2_kernel(const float* __restrict__ part, int n_strips, int n_rows,
+                                                             int r0, int rows, int cap, float* __restrict__ out) {
+  __shared__ MergeShared sh;
+  const int rl = threadIdx.x % kMergeRows, grp = threadIdx.x / kMergeRows;
+  const int k = blockIdx.x * kMergeRows + rl;
+  float M, S, U;
+  merge_strips(part, (int64_t)n_strips * n_rows, n_strips, n_rows, r0 + min(k, rows - 1), rl, grp, sh, M, S, U);
+  if (grp == 0 && k < cap) out[k] = k < rows ? M + log2f(S) : 0.0f;
 }
 
 struct DivParams {
@@ -1331,9 +1407,9 @@ struct DivParams {
 };
 
 // The measures of the pass rows from the pi kernel's sums (one per 128
-// vocabulary rows), taken against mu's lse A_q.  A workgroup takes 32 rows;
-// its 8 thread groups add the parts s = g, g + 8, ... of each row, and one
-// thread per row adds the 8 group sums in order.  With D = A_p - A_q (nats)
+// vocabulary rows), taken against mu's lse A_q.  A workgroup takes 16 rows;
+// its 16 thread groups add the parts s = g, g + 16, ... of each row, and one
+// thread per row adds the group sums in order.  With D = A_p - A_q (nats)
 // and r = exp(-D), so that p = r pt:
 //   KL(pi||mu) = sum p ((z - zq) - D) = r sum pt (z - zq) - D,
 //   KL(mu||pi) = sum q ((zq - z) + D) = sum q (zq - z) + D,
@@ -1348,11 +1424,12 @@ struct DivParams {
 // parts added in fp64 here, so the error of the result is about 3e-7 times
 // the sum of their magnitudes: the distance is NaN where that exceeds 1 % of
 // |p - q|^2 plus 1e-8 (an error above ~1e-4 on the distance).
-constexpr int kFinRows = 32, kFinGroups = 8;
-__global__ __launch_bounds__(kFinRows * kFinGroups) void div_finalize_kernel(DivParams p) {
-  __shared__ double part_sums[5][kFinGroups][kFinRows];
-  const int rl = threadIdx.x % kFinRows, grp = threadIdx.x / kFinRows;
-  const int k = blockIdx.x * kFinRows + rl;
+__global__ __launch_bounds__(kMergeThreads) void div_finalize_kernel(DivParams p) {
+  constexpr int kFinGroups = kMergeGroups;
+  __shared__ double part_sums[5][kFinGroups][kMergeRows];
+  __shared__ MergeShared sh;
+  const int rl = threadIdx.x % kMergeRows, grp = threadIdx.x / kMergeRows;
+  const int k = blockIdx.x * kMergeRows + rl;
   const bool in = k < p.rows;
   const int r = p.r0 + (in ? k : 0);
   const bool active = in && (p.mask ? p.mask[r] != 0 : true);
@@ -1365,7 +1442,8 @@ __global__ __launch_bounds__(kFinRows * kFinGroups) void div_finalize_kernel(Div
   }
 #pragma unroll
   for (int c = 0; c < 5; ++c) part_sums[c][grp][rl] = sum[c];
-  __syncthreads();
+  float Mp, Sp, Up;
+  merge_strips(p.part_pi, (int64_t)p.n_strips * p.n_rows, p.n_strips, p.n_rows, r, rl, grp, sh, Mp, Sp, Up);
   if (grp != 0 || !in) return;
   float kpm = 0.f, kmp = 0.f, l2 = 0.f;
   if (active) {
@@ -1374,7 +1452,7 @@ __global__ __launch_bounds__(kFinRows * kFinGroups) void div_finalize_kernel(Div
       sum[c] = part_sums[c][0][rl];
       for (int g2 = 1; g2 < kFinGroups; ++g2) sum[c] += part_sums[c][g2][rl];
     }
-    const float ap = merged_lse2(p.part_pi, (int64_t)p.n_strips * p.n_rows, p.n_strips, p.n_rows, r);
+    const float ap = Mp + log2f(Sp);
     const double D = ((double)ap - (double)p.aq2[k]) * (double)kLn2;
     // (infinite logits leave non-finite sums)
     bool finite = true;
@@ -1411,38 +1489,37 @@ struct MergeParams {
   float* lse[2];
   float* zout[2];
   int32_t* error_flag;
-  int q_begin, q_end;      // policies merged: [q_begin, q_end) of {pi, mu}
+  int q_begin;             // first policy merged of {pi, mu} (the grid's y extent: how many)
 };
 
-// One thread per row: combine the strips' states of pi and / or mu.
-__global__ __launch_bounds__(256) void merge_kernel(MergeParams p) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= p.n_rows) return;
+// The strips' states of pi (blockIdx.y = 0, from p.q_begin) and mu combined
+// per row.
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeParams p) {
+  __shared__ MergeShared sh;
+  const int rl = threadIdx.x % kMergeRows, grp = threadIdx.x / kMergeRows;
+  const int r = blockIdx.x * kMergeRows + rl;
+  const int q = p.q_begin + (int)blockIdx.y;
+  float M, S, U;
+  merge_strips(p.part[q], (int64_t)p.n_strips * p.n_rows, p.n_strips, p.n_rows, min(r, p.n_rows - 1), rl, grp, sh, M,
+               S, U);
+  if (grp != 0 || r >= p.n_rows) return;
   const int slot = p.out_slot ? p.out_slot[r] : r;
   const bool active = p.mask ? p.mask[r] != 0 : true;
   const int id = p.ids[r];
   const bool id_ok = id >= 0 && id < p.V;
   if (active && !id_ok && p.error_flag) atomicOr(p.error_flag, 1);
-  const int64_t plane = (int64_t)p.n_strips * p.n_rows;
-  for (int q = p.q_begin; q < p.q_end; ++q) {
-    float lse = 0.f, ent = 0.f, lp = 0.f, z = 0.f;
-    if (active) {
-      float M = kInitMax, S = 0.f, U = 0.f;
-      for (int s = 0; s < p.n_strips; ++s) {
-        const int64_t o = (int64_t)s * p.n_rows + r;
-        merge_state(M, S, U, p.part[q][o], p.part[q][plane + o], p.part[q][2 * plane + o]);
-      }
-      const float l2s = log2f(S);
-      lse = (M + l2s) * kLn2;
-      ent = (l2s - U / S) * kLn2;
-      z = id_ok ? p.logit[q][r] : __builtin_nanf("");
-      lp = z - lse;
-    }
-    p.logp[q][slot] = lp;
-    if (p.entropy[q]) p.entropy[q][slot] = ent;
-    if (p.lse[q]) p.lse[q][slot] = lse;
-    if (p.zout[q]) p.zout[q][slot] = z;
+  float lse = 0.f, ent = 0.f, lp = 0.f, z = 0.f;
+  if (active) {
+    const float l2s = log2f(S);
+    lse = (M + l2s) * kLn2;
+    ent = (l2s - U / S) * kLn2;
+    z = id_ok ? p.logit[q][r] : __builtin_nanf("");
+    lp = z - lse;
   }
+  p.logp[q][slot] = lp;
+  if (p.entropy[q]) p.entropy[q][slot] = ent;
+  if (p.lse[q]) p.lse[q][slot] = lse;
+  if (p.zout[q]) p.zout[q][slot] = z;
 }
 
 struct SampleMergeParams {
@@ -1456,29 +1533,48 @@ struct SampleMergeParams {
   float* logp;
 };
 
-// One thread per row: the sampled row is the strips' best Gumbel key (the
-// smaller row on a tie); its log-probability is its logit minus the merged
-// log-sum-exp.
-__global__ __launch_bounds__(256) void sample_merge_kernel(SampleMergeParams p) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= p.n_rows) return;
-  const int64_t plane = (int64_t)p.n_strips * p.n_rows;
-  float M = kInitMax, S = 0.f, U = 0.f;
-  float bk = -INFINITY, bz = 0.f;
-  int bi = 0;
-  for (int s = 0; s < p.n_strips; ++s) {
-    const int64_t o = (int64_t)s * p.n_rows + r;
-    merge_state(M, S, U, p.part[o], p.part[plane + o], p.part[2 * plane + o]);
+// The sampled row is the strips' best Gumbel key (the smaller row on a tie);
+// its log-probability is its logit minus the merged log-sum-exp.
+__global__ __launch_bounds__(kMergeThreads) void sample_merge_kernel(SampleMergeParams p) {
+  __shared__ MergeShared sh;
+  __shared__ float key[kMergeGroups][kMergeRows];
+  __shared__ int best[kMergeGroups][kMergeRows], where[kMergeGroups][kMergeRows];
+  const int rl = threadIdx.x % kMergeRows, grp = threadIdx.x / kMergeRows;
+  const int r = blockIdx.x * kMergeRows + rl;
+  const int rc = min(r, p.n_rows - 1);
+  float bk = -INFINITY;
+  int bi = 0, bs = 0;  // (no key above -inf: row 0 with logit 0)
+  bool any = false;
+#pragma unroll 4
+  for (int s = grp; s < p.n_strips; s += kMergeGroups) {
+    const int64_t o = (int64_t)s * p.n_rows + rc;
     const float k = p.best_key[o];
     const int i = p.best_id[o];
     if (k > bk || (k == bk && i < bi)) {
       bk = k;
-      bz = p.best_logit[o];
       bi = i;
+      bs = s;
+      any = true;
+    }
+  }
+  key[grp][rl] = bk;
+  best[grp][rl] = bi;
+  where[grp][rl] = any ? bs : -1;
+  float M, S, U;
+  merge_strips(p.part, (int64_t)p.n_strips * p.n_rows, p.n_strips, p.n_rows, rc, rl, grp, sh, M, S, U);
+  if (grp != 0 || r >= p.n_rows) return;
+  bs = where[0][rl];
+  for (int k = 1; k < kMergeGroups; ++k) {
+    const float k2 = key[k][rl];
+    const int i2 = best[k][rl];
+    if (where[k][rl] >= 0 && (k2 > bk || (k2 == bk && i2 < bi))) {
+      bk = k2;
+      bi = i2;
+      bs = where[k][rl];
     }
   }
   p.ids[r] = bi;
-  if (p.logp) p.logp[r] = bz - (M + log2f(S)) * kLn2;
+  if (p.logp) p.logp[r] = (bs >= 0 ? p.best_logit[(int64_t)bs * p.n_rows + r] : 0.0f) - (M + log2f(S)) * kLn2;
 }
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -1513,47 +1609,87 @@ hipError_t launch_pack_weights(const void* w, const void* wq, const void* wq_sca
   return hipGetLastError();
 }
 
-ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows, bool prepacked) {
+// Raster of n_ttiles token tiles x n_strips strips: blocks of block_t x
+// block_s units (about kBlockUnits, the units one XCD holds at a time).  Few
+// token tiles give narrow blocks of more strips, and few units give smaller
+// blocks, so that every XCD has a block of its own where there are 8 units.
+Raster raster_blocks(int n_ttiles, int n_strips) {
+  Raster r{};
+  n_ttiles = std::max(n_ttiles, 1);
+  r.n_tblocks = (n_ttiles + kBlockT - 1) / kBlockT;
+  r.block_t = (n_ttiles + r.n_tblocks - 1) / r.n_tblocks;
+  r.block_s = std::max(1, kBlockUnits / r.block_t);
+  r.block_s = std::min<int64_t>(r.block_s, ((int64_t)n_strips * r.n_tblocks + kXcds - 1) / kXcds);
+  r.n_sblocks = (n_strips + r.block_s - 1) / r.block_s;
+  r.n_blocks = r.n_tblocks * r.n_sblocks;
+  r.grid = (r.n_blocks + kXcds - 1) / kXcds * kXcds * r.block_t * r.block_s;
+  return r;
+}
+
+static void set_raster(ScoreParams& p, const Raster& r) {
+  p.n_tblocks = r.n_tblocks;
+  p.block_t = r.block_t;
+  p.block_s = r.block_s;
+  p.n_blocks = r.n_blocks;
+}
+
+ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows, bool prepacked, bool narrow) {
   ScorePlan pl{};
-  pl.n_ttiles = (int)((n_rows + kTileT - 1) / kTileT);
+  pl.n_ptiles = (int)((n_rows + kTileT - 1) / kTileT);
   pl.n_vtiles = (int)((V + kTileV - 1) / kTileV);
-  pl.n_tblocks = (pl.n_ttiles + kBlockT - 1) / kBlockT;
-  // Strips: a multiple of kBlockS (or every tile its own strip when there
-  // are fewer tiles), at most kMaxTilesPerStrip tiles each.  One workgroup
-  // per CU (256 CUs): minimise the makespan ceil(grid / 256) *
-  // (tiles-per-strip + 1/2), the half tile standing for a workgroup's fixed
-  // cost (prologue, state merge, partial writes); ties -> fewer strips.  The
-  // cap bounds a workgroup's duration: workgroup times differ by up to ~7 %
-  // between XCDs and CUs, and the last workgroups of a CU end spread over
-  // about one workgroup time (measured on the MI355X: 75-tile strips at
-  // d = 4096 take ~8 ms and left ~4 % of the CU time idle; 15-19-tile
-  // strips ran the pi and mu kernels 2-3 % faster).
+  // Token tile and strips: minimise the makespan of one persistent workgroup
+  // per CU (256 CUs), ceil(units / 256) * (tiles-per-strip + 1/2) * the tile's
+  // time, the half tile standing for a unit's fixed cost (prologue, last
+  // epilogue, state merge, partial writes); ties -> fewer strips, narrower
+  // tiles.  A call cannot be faster than the stream of W from HBM, which is
+  // worth 0.9 of a 256-token tile per vocabulary tile and CU (d = 4096 pi:
+  // 2 MiB at 5.5 TB/s / 256 CUs, 97 us, against 108 us for the tile).
+  // Tile times against 256 tokens, measured at d = 2048-5120, V = 151936: 0.5
+  // for 64 and 0.645 for 128 (their fragment reads from LDS, 1.25 per MFMA
+  // instead of 0.75, take longer than the MFMAs).  So (d = 4096, pi + mu +
+  // merge, us): 64 tokens 227 + 130 with 64-token tiles; 133 tokens 383 + 205
+  // with 64, 368 + 190 with 128, 335 + 178 with 256; 300 tokens 532 + 265 with
+  // 128, 583 + 291 with 256.
+  // At most kMaxTilesPerStrip tiles a strip: it bounds a unit's duration.
+  // Workgroup times differ by up to ~7 % between XCDs and CUs, and the last
+  // workgroups of a CU end spread over about one unit (75-tile strips at
+  // d = 4096 take ~8 ms and left ~4 % of the CU time idle; 15-19-tile strips
+  // ran the pi and mu kernels 2-3 % faster).
   constexpr int kMaxTilesPerStrip = 20;
-  const int64_t cus = 256;
+  constexpr int64_t kCus = 256;
+  // (strip, row) states the workspace holds: it grows with n_rows (a
+  // workspace sized for many rows serves fewer), whatever the strips chosen
+  const int64_t min_strips = (pl.n_vtiles + kMaxTilesPerStrip - 1) / kMaxTilesPerStrip;
+  const size_t strip_rows = (size_t)pl.n_vtiles * (size_t)std::min<int64_t>(n_rows, kTileT) +
+                            (size_t)std::max<int64_t>(64, min_strips) * (size_t)std::max<int64_t>(n_rows - kTileT, 0);
+  const double stream = 0.9 * pl.n_vtiles / (double)kCus;
   int best_s = 0;
-  int64_t best_cost = -1;
-  auto consider = [&](int s) {
-    const int tps = (pl.n_vtiles + s - 1) / s;
-    if (tps > kMaxTilesPerStrip) return;  // always reachable: s = n_vtiles gives 1 or 2
-    const int strips = (pl.n_vtiles + tps - 1) / tps;
-    const int sblocks = (strips + kBlockS - 1) / kBlockS;
-    int blocks = pl.n_tblocks * sblocks;
-    blocks = (blocks + kXcds - 1) / kXcds * kXcds;
-    const int64_t grid = (int64_t)blocks * kBlockT * kBlockS;
-    const int64_t cost = ((grid + cus - 1) / cus) * (2 * tps + 1);
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
-      best_s = strips;
+  double best_cost = -1.0;
+  auto consider = [&](int tile_t, double tile_cost) {
+    const int64_t n_tt = std::max<int64_t>((n_rows + tile_t - 1) / tile_t, 1);
+    for (int tps = kMaxTilesPerStrip; tps >= 1; --tps) {
+      const int strips = (pl.n_vtiles + tps - 1) / tps;
+      if ((size_t)strips * (size_t)n_rows > strip_rows) continue;  // (never at kMaxTilesPerStrip)
+      const int64_t rounds = (n_tt * strips + kCus - 1) / kCus;
+      const double cost = std::max((double)rounds * (tps + 0.5) * tile_cost, stream);
+      if (best_cost < 0 || cost < best_cost) {
+        best_cost = cost;
+        best_s = strips;
+        pl.tile_t = tile_t;
+      }
     }
   };
-  if (pl.n_vtiles <= kBlockS) consider(pl.n_vtiles);
-  for (int s = kBlockS; s <= pl.n_vtiles; s += kBlockS) consider(s);
+  // (the measures' passes take 256-token tiles only)
+  if (narrow && div_rows == 0) {
+    consider(64, 0.5);
+    consider(128, 0.645);
+  }
+  consider(kTileT, 1.0);
+  pl.n_ttiles = (int)((n_rows + pl.tile_t - 1) / pl.tile_t);
   pl.tiles_per_strip = (pl.n_vtiles + best_s - 1) / best_s;
   pl.n_strips = (pl.n_vtiles + pl.tiles_per_strip - 1) / pl.tiles_per_strip;
-  pl.n_sblocks = (pl.n_strips + kBlockS - 1) / kBlockS;
-  pl.n_blocks_pad = (pl.n_tblocks * pl.n_sblocks + kXcds - 1) / kXcds * kXcds;
-  pl.grid = pl.n_blocks_pad * kBlockT * kBlockS;
-  const size_t part_bytes = align_up((size_t)3 * pl.n_strips * (size_t)n_rows * sizeof(float), 256);
+  pl.raster = raster_blocks(pl.n_ttiles, pl.n_strips);
+  const size_t part_bytes = align_up((size_t)3 * strip_rows * sizeof(float), 256);
   const size_t logit_bytes = align_up((size_t)n_rows * sizeof(float), 256);
   size_t off = 0;
   for (int q = 0; q < 2; ++q) {
@@ -1566,11 +1702,11 @@ ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows, boo
   }
   // sampling: the strips' best Gumbel key, its logit and row
   pl.ws_best_offset = off;
-  off += 3 * align_up((size_t)pl.n_strips * (size_t)n_rows * sizeof(float), 256);
+  off += 3 * align_up(strip_rows * sizeof(float), 256);
   // packed operands: W, H (2d bytes per row), Wq, Hq (d bytes per row);
   // the weight images (W, Wq and Wq's MX scales) only when they do not come
   // prepacked by the caller
-  const size_t vrows = (size_t)pl.n_vtiles * kTileV, trows = (size_t)pl.n_ttiles * kTileT;
+  const size_t vrows = (size_t)pl.n_vtiles * kTileV, trows = (size_t)pl.n_ptiles * kTileT;
   const size_t pack_bytes[4] = {vrows * 2 * (size_t)d, trows * 2 * (size_t)d, vrows * (size_t)d, trows * (size_t)d};
   for (int q = 0; q < 4; ++q) {
     pl.ws_pack_offset[q] = off;
@@ -1590,7 +1726,7 @@ ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows, boo
   pl.div_tiles = 0;
   if (div_rows > 0) {
     const int64_t req = std::max<int64_t>((div_rows + kTileT - 1) / kTileT, 1);
-    const int64_t tiles = std::max<int64_t>(pl.n_ttiles, 1);
+    const int64_t tiles = std::max<int64_t>(pl.n_ptiles, 1);
     const int64_t passes = (tiles + req - 1) / req;
     pl.div_tiles = (int)((tiles + passes - 1) / passes);
     const size_t prow = (size_t)pl.div_tiles * kTileT;
@@ -1611,7 +1747,7 @@ ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows, boo
 hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStream_t s) {
   if (dsc.n_rows == 0) return hipSuccess;
   uint8_t* ws = static_cast<uint8_t*>(dsc.workspace);
-  const unsigned grid = (unsigned)pl.grid;
+  const unsigned grid = (unsigned)pl.raster.grid;
 
   ScoreParams pp{};
   pp.V = (int)dsc.V;
@@ -1620,7 +1756,7 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
   pp.tiles_per_strip = pl.tiles_per_strip;
   pp.n_strips = pl.n_strips;
   pp.n_ttiles = pl.n_ttiles;
-  pp.n_tblocks = pl.n_tblocks;
+  set_raster(pp, pl.raster);
   pp.inv_temp = dsc.inv_temperature;
   pp.ids = dsc.token_ids;
   pp.mx_row_bytes = (int)(dsc.d / 32);
@@ -1635,7 +1771,7 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
   // the caller did not pass them prepacked)
   const void* srcs[4] = {dsc.w, dsc.h, dsc.wq, dsc.hq};
   const int64_t src_rows[4] = {dsc.V, dsc.n_rows, dsc.V, dsc.n_rows};
-  const int64_t src_tiles[4] = {pl.n_vtiles, pl.n_ttiles, pl.n_vtiles, pl.n_ttiles};
+  const int64_t src_tiles[4] = {pl.n_vtiles, pl.n_ptiles, pl.n_vtiles, pl.n_ptiles};
   for (int q = 0; q < 4; ++q) {
     if (!(q < 2 ? do_pi : do_mu)) continue;
     if (pw && (q == 0 || q == 2)) continue;
@@ -1662,7 +1798,7 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
   pm.logit = reinterpret_cast<float*>(ws + pl.ws_logit_offset[1]);
   if (dsc.mu_scaling == ACRL_SCALE_MX32) {
     if (do_mu && !pw) launch_pack_mx(dsc.wq_scales, dsc.V, dsc.d, pl.n_vtiles, ws + pl.ws_mx_offset[0], s);
-    if (do_mu) launch_pack_mx(dsc.hq_scales, dsc.n_rows, dsc.d, pl.n_ttiles, ws + pl.ws_mx_offset[1], s);
+    if (do_mu) launch_pack_mx(dsc.hq_scales, dsc.n_rows, dsc.d, pl.n_ptiles, ws + pl.ws_mx_offset[1], s);
     pm.a_mx = pw ? pw + pwl.mx_offset : ws + pl.ws_mx_offset[0];
     pm.b_mx = ws + pl.ws_mx_offset[1];
   } else {
@@ -1672,15 +1808,15 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
   auto launch_mu = [&](const ScoreParams& q, unsigned g, auto epi_tag) {
     constexpr int E = decltype(epi_tag)::value;
     if (dsc.mu_scaling == ACRL_SCALE_MX32)
-      launch_score_kernel<kMX, E>(g, q, s);
+      launch_score_kernel<kMX, E>(g, q, s, pl.tile_t);
     else if (dsc.mu_scaling == ACRL_SCALE_PER_ROW)
-      launch_score_kernel<kFP8Row, E>(g, q, s);
+      launch_score_kernel<kFP8Row, E>(g, q, s, pl.tile_t);
     else
-      launch_score_kernel<kFP8Tensor, E>(g, q, s);
+      launch_score_kernel<kFP8Tensor, E>(g, q, s, pl.tile_t);
   };
   const bool div = dsc.kl_pi_mu || dsc.kl_mu_pi || dsc.l2;  // both policies (checked by the caller)
   if (!div) {
-    if (do_pi) launch_score_kernel<kBF16, kEpiSoftmax>(grid, pp, s);
+    if (do_pi) launch_score_kernel<kBF16, kEpiSoftmax>(grid, pp, s, pl.tile_t);
     if (do_mu) launch_mu(pm, grid, std::integral_constant<int, kEpiSoftmax>{});
   } else {
     // passes of div_tiles token tiles: mu (softmax + its logits stored),
@@ -1692,22 +1828,22 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
     const int cap = pl.div_tiles * kTileT;
     for (int tt0 = 0; tt0 < pl.n_ttiles; tt0 += pl.div_tiles) {
       const int nt = std::min(pl.div_tiles, pl.n_ttiles - tt0);
-      const int ntb = (nt + kBlockT - 1) / kBlockT;
-      const unsigned g = (unsigned)((ntb * pl.n_sblocks + kXcds - 1) / kXcds * kXcds * kBlockT * kBlockS);
+      const Raster rs = raster_blocks(nt, pl.n_strips);
+      const unsigned g = (unsigned)rs.grid;
       const int r0 = tt0 * kTileT;
       const int rows = (int)std::min<int64_t>(dsc.n_rows - r0, (int64_t)nt * kTileT);
       ScoreParams pq = pm;
       pq.tt_offset = tt0;
       pq.n_ttiles = nt;
-      pq.n_tblocks = ntb;
+      set_raster(pq, rs);
       pq.zbuf = zq;
       launch_mu(pq, g, std::integral_constant<int, kEpiSoftmaxZ>{});
-      hipLaunchKernelGGL(lse2_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), 0, s, pm.part, pl.n_strips,
+      hipLaunchKernelGGL(lse2_kernel, dim3((unsigned)((cap + kMergeRows - 1) / kMergeRows)), dim3(kMergeThreads), 0, s, pm.part, pl.n_strips,
                          (int)dsc.n_rows, r0, rows, cap, aq2);
       ScoreParams pz = pp;
       pz.tt_offset = tt0;
       pz.n_ttiles = nt;
-      pz.n_tblocks = ntb;
+      set_raster(pz, rs);
       pz.zbuf = zq;
       pz.aq2 = aq2;
       pz.dpart = dpart;
@@ -1728,8 +1864,8 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
       dp.kl_pm = dsc.kl_pi_mu;
       dp.kl_mp = dsc.kl_mu_pi;
       dp.l2 = dsc.l2;
-      hipLaunchKernelGGL(div_finalize_kernel, dim3((unsigned)((rows + kFinRows - 1) / kFinRows)),
-                         dim3(kFinRows * kFinGroups), 0, s, dp);
+      hipLaunchKernelGGL(div_finalize_kernel, dim3((unsigned)((rows + kMergeRows - 1) / kMergeRows)),
+                         dim3(kMergeThreads), 0, s, dp);
     }
   }
 
@@ -1750,8 +1886,8 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
   mp.zout[0] = dsc.logit_pi;      mp.zout[1] = dsc.logit_mu;
   mp.error_flag = dsc.error_flag;
   mp.q_begin = do_pi ? 0 : 1;
-  mp.q_end = do_mu ? 2 : 1;
-  hipLaunchKernelGGL(merge_kernel, dim3((unsigned)((dsc.n_rows + 255) / 256)), dim3(256), 0, s, mp);
+  hipLaunchKernelGGL(merge_kernel, dim3((unsigned)((dsc.n_rows + kMergeRows - 1) / kMergeRows), do_pi && do_mu ? 2u : 1u),
+                     dim3(kMergeThreads), 0, s, mp);
   return hipGetLastError();
 }
 
@@ -1764,10 +1900,9 @@ static void gemm_grid(int n_atiles, int n_btiles, ScoreParams& pp, unsigned& gri
   pp.tiles_per_strip = 1;
   pp.n_strips = n_atiles;
   pp.n_ttiles = n_btiles;
-  pp.n_tblocks = (n_btiles + kBlockT - 1) / kBlockT;
-  const int n_sblocks = (n_atiles + kBlockS - 1) / kBlockS;
-  const int blocks = (pp.n_tblocks * n_sblocks + kXcds - 1) / kXcds * kXcds;
-  grid = (unsigned)(blocks * kBlockT * kBlockS);
+  const Raster r = raster_blocks(n_btiles, n_atiles);
+  set_raster(pp, r);
+  grid = (unsigned)r.grid;
 }
 
 BackwardPlan plan_backward(int64_t n_rows, int64_t d, int64_t V, int64_t chunk) {
@@ -1838,7 +1973,7 @@ hipError_t launch_backward(const acrl_backward_desc& dsc, const BackwardPlan& pl
                          rows, d, kch_t, img_ht);
     // dZ of the chunk from the recomputed logits (vocabulary strips as in scoring)
     {
-      const ScorePlan sp = plan_score(rows, d, V);
+      const ScorePlan sp = plan_score(rows, d, V, 0, true, false);
       ScoreParams pg{};
       pg.a = img_w;
       pg.b = img_h;
@@ -1849,7 +1984,7 @@ hipError_t launch_backward(const acrl_backward_desc& dsc, const BackwardPlan& pl
       pg.tiles_per_strip = sp.tiles_per_strip;
       pg.n_strips = sp.n_strips;
       pg.n_ttiles = sp.n_ttiles;
-      pg.n_tblocks = sp.n_tblocks;
+      set_raster(pg, sp.raster);
       pg.inv_temp = dsc.inv_temperature;
       pg.ids = dsc.token_ids + r0;
       pg.g_coef = dsc.coef;
@@ -1860,7 +1995,7 @@ hipError_t launch_backward(const acrl_backward_desc& dsc, const BackwardPlan& pl
       pg.gz_v = img_zv;
       pg.kch_v = pl.kch_v;
       pg.kch_t = kch_t;
-      launch_score_kernel<kBF16, kEpiGrad>((unsigned)sp.grid, pg, s);
+      launch_score_kernel<kBF16, kEpiGrad>((unsigned)sp.raster.grid, pg, s);
     }
     // dH[chunk] = dZ W: A = dZ (rows = tokens), B = W^T (rows = d), K = vocabulary
     if (dh) {
@@ -1907,7 +2042,7 @@ hipError_t launch_sample(const acrl_sample_desc& dsc, const ScorePlan& pl, hipSt
   const PackedWeightsLayout pwl = packed_weights_layout(dsc.V, dsc.d, dsc.mu_scaling);
   const void* srcs[2] = {dsc.wq, dsc.hq};
   const int64_t src_rows[2] = {dsc.V, dsc.n_rows};
-  const int64_t src_tiles[2] = {pl.n_vtiles, pl.n_ttiles};
+  const int64_t src_tiles[2] = {pl.n_vtiles, pl.n_ptiles};
   for (int q = 0; q < 2; ++q) {
     if (q == 0 && pw) continue;  // Wq comes prepacked
     const int64_t units = src_tiles[q] * kTileV * (dsc.d / 16);
@@ -1922,7 +2057,7 @@ hipError_t launch_sample(const acrl_sample_desc& dsc, const ScorePlan& pl, hipSt
   pm.tiles_per_strip = pl.tiles_per_strip;
   pm.n_strips = pl.n_strips;
   pm.n_ttiles = pl.n_ttiles;
-  pm.n_tblocks = pl.n_tblocks;
+  set_raster(pm, pl.raster);
   pm.inv_temp = dsc.inv_temperature;
   pm.mx_row_bytes = (int)(dsc.d / 32);
   pm.queue = reinterpret_cast<int*>(ws + pl.ws_queue_offset);
@@ -1937,20 +2072,20 @@ hipError_t launch_sample(const acrl_sample_desc& dsc, const ScorePlan& pl, hipSt
   pm.best_key = reinterpret_cast<float*>(ws + pl.ws_best_offset);
   pm.best_logit = reinterpret_cast<float*>(ws + pl.ws_best_offset + best_plane);
   pm.best_id = reinterpret_cast<int32_t*>(ws + pl.ws_best_offset + 2 * best_plane);
-  const unsigned grid = (unsigned)pl.grid;
+  const unsigned grid = (unsigned)pl.raster.grid;
   if (dsc.mu_scaling == ACRL_SCALE_MX32) {
     if (!pw) launch_pack_mx(dsc.wq_scales, dsc.V, dsc.d, pl.n_vtiles, ws + pl.ws_mx_offset[0], s);
-    launch_pack_mx(dsc.hq_scales, dsc.n_rows, dsc.d, pl.n_ttiles, ws + pl.ws_mx_offset[1], s);
+    launch_pack_mx(dsc.hq_scales, dsc.n_rows, dsc.d, pl.n_ptiles, ws + pl.ws_mx_offset[1], s);
     pm.a_mx = pw ? pw + pwl.mx_offset : ws + pl.ws_mx_offset[0];
     pm.b_mx = ws + pl.ws_mx_offset[1];
-    launch_score_kernel<kMX, kEpiSample>(grid, pm, s);
+    launch_score_kernel<kMX, kEpiSample>(grid, pm, s, pl.tile_t);
   } else {
     pm.a_scale = static_cast<const float*>(dsc.wq_scales);
     pm.b_scale = static_cast<const float*>(dsc.hq_scales);
     if (dsc.mu_scaling == ACRL_SCALE_PER_ROW)
-      launch_score_kernel<kFP8Row, kEpiSample>(grid, pm, s);
+      launch_score_kernel<kFP8Row, kEpiSample>(grid, pm, s, pl.tile_t);
     else
-      launch_score_kernel<kFP8Tensor, kEpiSample>(grid, pm, s);
+      launch_score_kernel<kFP8Tensor, kEpiSample>(grid, pm, s, pl.tile_t);
   }
   SampleMergeParams mp{};
   mp.n_rows = (int)dsc.n_rows;
@@ -1961,7 +2096,8 @@ hipError_t launch_sample(const acrl_sample_desc& dsc, const ScorePlan& pl, hipSt
   mp.best_id = pm.best_id;
   mp.ids = dsc.ids;
   mp.logp = dsc.logp_mu;
-  hipLaunchKernelGGL(sample_merge_kernel, dim3((unsigned)((dsc.n_rows + 255) / 256)), dim3(256), 0, s, mp);
+  hipLaunchKernelGGL(sample_merge_kernel, dim3((unsigned)((dsc.n_rows + kMergeRows - 1) / kMergeRows)),
+                     dim3(kMergeThreads), 0, s, mp);
   return hipGetLastError();
 }
 

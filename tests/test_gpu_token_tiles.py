@@ -1,0 +1,73 @@
+"""Token tiles of 64, 128 and 256 rows (calls of few tokens): the logits and
+the draws do not depend on the tile width or on the vocabulary strips that a
+call's row count selects, and each width matches the oracle at its edges.
+Row counts at and beside the tile widths, on a head of many vocabulary tiles
+(several per strip) and on one of few."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+from cases import TOL_LOGP, random_bf16, tol_entropy
+from gpu_util import down, torch_dev, up, up_bf16
+
+D = 128
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scaling", [oracle.PER_TENSOR, oracle.PER_ROW, oracle.MX32])
+@pytest.mark.parametrize("V", [2100, 151936])
+def test_token_tile_widths(scaling, V):
+    torch, dev = torch_dev()
+    from paper_2607_24062_amd import acrl
+    T = 1030
+    H = random_bf16((T, D), 21)
+    W = random_bf16((V, D), 22, std=2.5 / D ** 0.5)
+    ids = np.random.default_rng(23).integers(0, V, size=T).astype(np.int32)
+    h, w, idt = up_bf16(torch, dev, H), up_bf16(torch, dev, W), up(torch, dev, ids)
+    hq, hs = acrl.acrl_quantize_fp8(h, scaling)
+    wq, ws = acrl.acrl_quantize_fp8(w, scaling)
+    packed = acrl.acrl_pack_weights(w, wq, ws, scaling)
+
+    def rows(n):  # the first n rows in one call
+        s = hs if scaling == oracle.PER_TENSOR else hs[:n]
+        out = acrl.acrl_score_pi_mu(h[:n], w, hq[:n], s, wq, ws, scaling, idt[:n], packed_weights=packed)
+        draw, lm = acrl.acrl_sample_mu(hq[:n], s, wq, ws, scaling, seed=9, packed_weights=packed)
+        out = {k: down(v) for k, v in out.items()}
+        out["ids"], out["draw_logp"] = down(draw), down(lm)
+        return out
+
+    full = rows(T)
+    check = [0, 31, 63, 64, 100, 127, 128, 129, 255, 256]
+    hq_o, hs_o = oracle.quantize_fp8(H, scaling)
+    wq_o, ws_o = oracle.quantize_fp8(W, scaling)
+    sel = np.array(check)
+    ref = oracle.score(H[sel], W, hq_o[sel], hs_o if scaling == oracle.PER_TENSOR else hs_o[sel], wq_o, ws_o, scaling,
+                       ids[sel])
+    for n in (1, 64, 65, 128, 133, 256, 257, 400, 600):
+        got = rows(n)
+        for k in ("logit_pi", "logit_mu", "ids"):  # whatever the tiles: one order of every sum
+            assert np.array_equal(got[k], full[k][:n]), (k, n)
+        for k in ("logp_pi", "logp_mu", "entropy_pi", "entropy_mu", "draw_logp"):
+            # strips merge in another order: a few fp32 roundings of values up to ~20
+            np.testing.assert_allclose(got[k], full[k][:n], rtol=0, atol=1e-5, err_msg="%s %d" % (k, n))
+        m = sel < n
+        for tag, ent in (("pi", "ent_pi"), ("mu", "ent_mu")):
+            assert np.abs(got["logp_" + tag][sel[m]] - ref["logp_" + tag][m]).max() <= TOL_LOGP, (tag, n)
+            assert np.abs(got["entropy_" + tag][sel[m]] - ref[ent][m]).max() <= tol_entropy(V), (tag, n)
+
+
+def test_workspace_grows_with_rows():
+    """A workspace sized for many rows serves fewer, whatever tiles and strips
+    each row count selects (host arithmetic only)."""
+    from paper_2607_24062_amd import acrl
+    L = acrl.lib()
+    nb = ctypes.c_size_t()
+    for d, V in ((128, 100), (2048, 151936), (4096, 32003), (256, 600000)):
+        last = 0
+        for n in list(range(0, 1100)) + list(range(1100, 40000, 97)):
+            desc = acrl.ScoreDesc(n_rows=n, d=d, V=V, mu_scaling=acrl.SCALE_MX32, packed_weights=ctypes.c_void_p(256))
+            assert L.acrl_score_workspace_query(ctypes.byref(desc), ctypes.byref(nb)) == 0
+            assert nb.value >= last, (d, V, n)
+            last = nb.value
