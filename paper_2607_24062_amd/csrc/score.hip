@@ -115,6 +115,9 @@ struct ScoreParams {
   int64_t ldc;
   int c_rows;              // valid A rows (M)
   int c_accumulate;        // 1: C += product (C is read once before the K loop)
+  int n_atiles;            // A tiles; strip st is K slice st / n_atiles of A tile st % n_atiles
+  int k_slice;             // 64-byte K chunks per slice (even; all of them: one slice)
+  int64_t c_slice;         // floats between the slices' products
   // row chunks and the full-vocabulary measures (kEpiSoftmaxZ, kEpiSoftmaxDiv)
   int tt_offset;           // token tile of this launch's tile 0 (n_ttiles counts the launch's tiles)
   float* zbuf;             // mu's logits of the launch's rows (natural units), accumulator layout (zbuf_index)
@@ -351,9 +354,12 @@ void score_kernel(ScoreParams p) {
   if (tt >= p.n_ttiles || st >= p.n_strips) return;  // padding of the grid
   const int ttg = tt + p.tt_offset;  // token tile in the whole call
   const int t0 = ttg * TT;
-  const int vt_begin = st * p.tiles_per_strip;
-  const int vt_end = min(vt_begin + p.tiles_per_strip, p.n_vtiles);
-  const int n_iter = (vt_end - vt_begin) * p.n_chunks;
+  const int k_part = EPI == kEpiStore ? st / p.n_atiles : 0;  // plain product: the unit's K slice
+  const int kc0 = EPI == kEpiStore ? k_part * p.k_slice : 0;
+  const int n_kc = EPI == kEpiStore ? min(p.k_slice, p.n_chunks - kc0) : p.n_chunks;  // K chunks per tile
+  const int vt_begin = EPI == kEpiStore ? st - k_part * p.n_atiles : st * p.tiles_per_strip;
+  const int vt_end = EPI == kEpiStore ? vt_begin + 1 : min(vt_begin + p.tiles_per_strip, p.n_vtiles);
+  const int n_iter = (vt_end - vt_begin) * n_kc;
 
   // ---- per-lane tokens: column r32 of each of the wave's 4 token blocks
   int tok[4], id[4];
@@ -436,6 +442,7 @@ void score_kernel(ScoreParams p) {
     const int v0 = (vt_begin + q) * kTileV;
     const int a_rows = min(kTileV, p.V - v0);  // valid rows of the vocabulary tile
     const __amdgpu_buffer_rsrc_t rsrc_a = make_rsrc(p.a + (int64_t)(vt_begin + q) * tile_bytes, tile_bytes);
+    if constexpr (EPI == kEpiStore) kc += kc0;
     const uint32_t soff = (uint32_t)kc * kPackBlock + (uint32_t)wave_u * (kPackBlock / NW);
     uint8_t* la = stage_at(stg) + wave_u * (kPackBlock / NW);
     constexpr int kBWave = TT * kChunk / NW;  // bytes of the token tile per wave
@@ -910,6 +917,7 @@ void score_kernel(ScoreParams p) {
   // accumulating); m = A row, n = B row; 32 lanes store 32 consecutive n.
   auto store_epilogue = [&](int tile) {
     const int m0 = tile * kTileV + wv * 128 + 4 * g;
+    float* c = p.c + (int64_t)k_part * p.c_slice;
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -918,7 +926,7 @@ void score_kernel(ScoreParams p) {
         for (int i = 0; i < 16; ++i) {
           const int m = m0 + 32 * b + 8 * (i >> 2) + (i & 3);
           const float x = acc[b][j][i];  // (VGPR form: the 8-wave products)
-          if (m < p.c_rows && tok[j] < p.n_rows) p.c[(int64_t)m * p.ldc + tok[j]] = x;
+          if (m < p.c_rows && tok[j] < p.n_rows) c[(int64_t)m * p.ldc + tok[j]] = x;
         }
   };
 
@@ -934,7 +942,7 @@ void score_kernel(ScoreParams p) {
   constexpr int L = (MODE == kBF16) ? 2 : 1;
   int qi = 0, kci = 0;  // tile and chunk of the next chunk to request
   auto advance_issue = [&]() {
-    if (++kci == p.n_chunks) {
+    if (++kci == n_kc) {
       kci = 0;
       ++qi;
     }
@@ -1031,7 +1039,7 @@ void score_kernel(ScoreParams p) {
   for (int q = 0; q < vt_end - vt_begin; ++q) {
     // steady chunks: [0, kc_steady); the rest request nothing new or only
     // while requests remain, and wait for every load
-    const int kc_steady = min(p.n_chunks, max(0, n_iter - NS - it));
+    const int kc_steady = min(n_kc, max(0, n_iter - NS - it));
     int kc = 0;
     if constexpr (kZeroStart) {
     // the first pair (every tile has an even number >= 2 of chunks): its
@@ -1050,7 +1058,7 @@ void score_kernel(ScoreParams p) {
       chunk(std::true_type{}, std::false_type{}, it, f0, f1);
       chunk(std::true_type{}, std::false_type{}, it + 1, f1, f0);
     }
-    for (; kc < p.n_chunks; kc += 2, it += 2) {
+    for (; kc < n_kc; kc += 2, it += 2) {
       chunk(std::false_type{}, std::false_type{}, it, f0, f1);
       chunk(std::false_type{}, std::false_type{}, it + 1, f1, f0);
     }
@@ -1326,6 +1334,21 @@ __global__ __launch_bounds__(256) void pack_t_kernel(const uint16_t* __restrict_
   for (int c = 0; c < 4; ++c)
     *reinterpret_cast<uint4*>(row + ((c ^ ((t >> 2) & 3)) << 4)) =
         make_uint4(w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]);
+}
+
+// out (+)= the sum of n_slices consecutive arrays of n floats (fixed order).
+template <int VEC>
+__global__ __launch_bounds__(256) void sum_slices_kernel(const float* __restrict__ parts, int n_slices, int64_t n,
+                                                         bool accumulate, float* __restrict__ out) {
+  typedef float vec __attribute__((ext_vector_type(VEC)));
+  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC; i < n;
+       i += (int64_t)gridDim.x * blockDim.x * VEC) {
+    vec t = *reinterpret_cast<const vec*>(parts + i);
+#pragma unroll 4
+    for (int k = 1; k < n_slices; ++k) t += *reinterpret_cast<const vec*>(parts + k * n + i);
+    if (accumulate) t += *reinterpret_cast<const vec*>(out + i);
+    *reinterpret_cast<vec*>(out + i) = t;
+  }
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float* __restrict__ p, int64_t n) {
@@ -1892,17 +1915,45 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
 }
 
 // ------------------------------------------------------------------ backward
-// Grid of a plain product (kEpiStore): one unit per output tile, in the
-// scoring kernel's XCD-aware raster (A tiles play the vocabulary strips, B
-// tiles the token tiles).
-static void gemm_grid(int n_atiles, int n_btiles, ScoreParams& pp, unsigned& grid) {
+// Grid of a plain product (kEpiStore): one unit per output tile and K slice,
+// in the scoring kernel's XCD-aware raster (A tiles play the vocabulary
+// strips, B tiles the token tiles).
+static void gemm_grid(int n_atiles, int n_btiles, int n_slices, ScoreParams& pp, unsigned& grid) {
   pp.n_vtiles = n_atiles;
+  pp.n_atiles = n_atiles;
   pp.tiles_per_strip = 1;
-  pp.n_strips = n_atiles;
+  pp.n_strips = n_atiles * n_slices;
   pp.n_ttiles = n_btiles;
-  const Raster r = raster_blocks(n_btiles, n_atiles);
+  const Raster r = raster_blocks(n_btiles, pp.n_strips);
   set_raster(pp, r);
   grid = (unsigned)r.grid;
+}
+
+// K slices of a product of `units` 256 x 256 output tiles and n_chunks 64-byte
+// chunks of K.  dH = dZ W has few tiles and the whole vocabulary as K, so a
+// pass of a few thousand rows leaves CUs idle (96 tiles on 256 CUs at 1531 x
+// 4096; 320, two rounds, at 10111 x 2048); dW of a small head is alike.
+// Slices of K are units of their own; their fp32 products are added in slice
+// order (sum_slices_kernel).  The time is estimated in chunks of one tile
+// (0.84 us): rounds of 256 units of a slice each, ~20 chunks a unit for the
+// pipeline fill and the 256 KiB stored, and the products written and read
+// back (5 TB/s: 16 tiles a chunk time).  Slices hold at least 64 chunks, and
+// all products of a split at most kSliceTiles tiles.
+constexpr int kMinSliceChunks = 64, kMaxSlices = 16, kSliceTiles = 2048;
+static int k_slices(int64_t units, int n_chunks) {
+  int best = 1;
+  double best_cost = 0;
+  for (int ks = 1; ks <= kMaxSlices; ++ks) {
+    if (ks > 1 && (n_chunks < ks * kMinSliceChunks || units * ks > kSliceTiles)) break;
+    const int per = ((n_chunks + ks - 1) / ks + 1) / 2 * 2;
+    const double traffic = ks > 1 ? (2 * ks + 1) * (double)units / 16 : 0.0;
+    const double cost = (double)((units * ks + 255) / 256) * (per + 20) + traffic;
+    if (ks == 1 || cost < best_cost) {
+      best = ks;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 BackwardPlan plan_backward(int64_t n_rows, int64_t d, int64_t V, int64_t chunk) {
@@ -1929,8 +1980,45 @@ BackwardPlan plan_backward(int64_t n_rows, int64_t d, int64_t V, int64_t chunk) 
   pl.off_zt = take((size_t)n_ttiles * kTileT * vrows * 2); // dZ, rows = tokens, K = vocabulary
   pl.off_zv = take(vrows * crows * 2);                     // dZ^T, rows = vocabulary, K = tokens
   pl.off_queue = take((size_t)kXcds * kQueueStride * sizeof(int));  // the products' claim counters
+  // products of K slices: dH's grow with the rows (a workspace sized for many
+  // rows serves fewer), dW's depend on the head alone
+  const int64_t dh_units = (int64_t)n_ttiles * pl.n_dtiles, dw_units = (int64_t)pl.n_vtiles * pl.n_dtiles;
+  const int64_t slice_tiles = std::max<int64_t>(std::min<int64_t>(kSliceTiles, kMaxSlices * dh_units),
+                                                2 * dw_units > kSliceTiles ? 0 : std::min<int64_t>(kSliceTiles, kMaxSlices * dw_units));
+  pl.off_slices = take((size_t)slice_tiles * kTileV * kTileT * sizeof(float));
   pl.ws_bytes = off;
   return pl;
+}
+
+// C[m, n] (+)= sum over K of A[m] B[n], row-major C of m_rows x n_cols floats.
+// slices: room for kSliceTiles tiles where k_slices splits K.
+static void launch_product(const uint8_t* a, const uint8_t* b, int n_atiles, int n_btiles, int n_chunks, int64_t m_rows,
+                           int64_t n_cols, bool accumulate, float* c, float* slices, int* queue, hipStream_t s) {
+  const int ks = k_slices((int64_t)n_atiles * n_btiles, n_chunks);
+  ScoreParams pc{};
+  unsigned grid = 0;
+  gemm_grid(n_atiles, n_btiles, ks, pc, grid);
+  pc.a = a;
+  pc.b = b;
+  pc.n_chunks = n_chunks;
+  pc.k_slice = ((n_chunks + ks - 1) / ks + 1) / 2 * 2;  // (no slice is empty: 2 ks < kMinSliceChunks)
+  pc.n_rows = (int)n_cols;
+  pc.V = (int)m_rows;
+  pc.c = ks > 1 ? slices : c;
+  pc.c_slice = m_rows * n_cols;
+  pc.ldc = n_cols;
+  pc.c_rows = (int)m_rows;
+  pc.c_accumulate = accumulate && ks == 1 ? 1 : 0;
+  pc.queue = queue;
+  launch_score_kernel<kBF16, kEpiStore>(grid, pc, s);
+  if (ks > 1) {
+    const int64_t n = m_rows * n_cols;  // a multiple of 4 (d is one of 128)
+    const unsigned blocks = (unsigned)std::min<int64_t>((n / 4 + 255) / 256, 4096);
+    if (((uintptr_t)c & 15) == 0)
+      hipLaunchKernelGGL(sum_slices_kernel<4>, dim3(blocks), dim3(256), 0, s, slices, ks, n, accumulate, c);
+    else
+      hipLaunchKernelGGL(sum_slices_kernel<1>, dim3(blocks), dim3(256), 0, s, slices, ks, n, accumulate, c);
+  }
 }
 
 hipError_t launch_backward(const acrl_backward_desc& dsc, const BackwardPlan& pl, hipStream_t s) {
@@ -1998,39 +2086,13 @@ hipError_t launch_backward(const acrl_backward_desc& dsc, const BackwardPlan& pl
       launch_score_kernel<kBF16, kEpiGrad>((unsigned)sp.raster.grid, pg, s);
     }
     // dH[chunk] = dZ W: A = dZ (rows = tokens), B = W^T (rows = d), K = vocabulary
-    if (dh) {
-      ScoreParams pc{};
-      unsigned grid = 0;
-      gemm_grid(n_ttiles, pl.n_dtiles, pc, grid);
-      pc.a = img_zt;
-      pc.b = img_wt;
-      pc.n_chunks = pl.kch_v;
-      pc.n_rows = (int)d;
-      pc.V = (int)rows;
-      pc.c = dh + r0 * d;
-      pc.ldc = d;
-      pc.c_rows = (int)rows;
-      pc.c_accumulate = 0;
-      pc.queue = reinterpret_cast<int*>(ws + pl.off_queue);
-      launch_score_kernel<kBF16, kEpiStore>(grid, pc, s);
-    }
+    float* slices = reinterpret_cast<float*>(ws + pl.off_slices);
+    int* queue = reinterpret_cast<int*>(ws + pl.off_queue);
+    if (dh) launch_product(img_zt, img_wt, n_ttiles, pl.n_dtiles, pl.kch_v, rows, d, false, dh + r0 * d, slices, queue, s);
     // dW (+)= dZ^T H: A = dZ^T (rows = vocabulary), B = H^T (rows = d), K = tokens
-    if (dw) {
-      ScoreParams pc{};
-      unsigned grid = 0;
-      gemm_grid(pl.n_vtiles, pl.n_dtiles, pc, grid);
-      pc.a = img_zv;
-      pc.b = img_ht;
-      pc.n_chunks = kch_t;
-      pc.n_rows = (int)d;
-      pc.V = (int)V;
-      pc.c = dw;
-      pc.ldc = d;
-      pc.c_rows = (int)V;
-      pc.c_accumulate = (r0 > 0 || dsc.accumulate_dw) ? 1 : 0;
-      pc.queue = reinterpret_cast<int*>(ws + pl.off_queue);
-      launch_score_kernel<kBF16, kEpiStore>(grid, pc, s);
-    }
+    if (dw)
+      launch_product(img_zv, img_ht, pl.n_vtiles, pl.n_dtiles, kch_t, V, d, r0 > 0 || dsc.accumulate_dw, dw, slices,
+                     queue, s);
   }
   return hipGetLastError();
 }
