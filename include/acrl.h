@@ -154,12 +154,14 @@ acrl_status acrl_fp8_encode(const float* x, int64_t n, int rounding, void* q, vo
  * for rows = V and rows = n_rows: (rows rounded up to 256) * d / 8 < 2^32;
  * token ids in [0, V) (else the row's outputs are NaN and *error_flag, if
  * given, becomes nonzero; the flag is never cleared by the library).
- * The workspace holds a tiled copy of W, h, Wq and hq and of the E8M0 scales
- * of Wq and hq (about (3 + 1/32) (V + n_rows) d bytes) besides the per-strip
- * partial states and the work-queue counters of the persistent launches
- * (cleared by the call itself); with packed_weights (acrl_pack_weights) the
- * copies of W and Wq come from there and the workspace holds only the
- * activations' (acrl_score_workspace_query).
+ * The workspace holds a tiled copy of h and hq and of the E8M0 scales of Wq and
+ * hq, for calls of many rows (above 12288) also of W and Wq (then about
+ * (3 + 1/32) (V + n_rows) d bytes; with fewer rows W and Wq are read where
+ * they lie), besides the per-strip partial states and the work-queue counters
+ * of the persistent launches (cleared by the call itself); with
+ * packed_weights (acrl_pack_weights) the copies of W and Wq come from there
+ * and the workspace holds only the activations' (acrl_score_workspace_query).
+ * Fewer rows never need a larger workspace (without the measures below).
  * policies = ACRL_POLICY_PI scores pi only (h, w, logp_pi required; the mu
  * fields are not read and the mu outputs not written), ACRL_POLICY_MU mu only;
  * the full-vocabulary measures need both.
@@ -474,7 +476,7 @@ acrl_status acrl_surrogate(const acrl_surrogate_desc* desc, void* stream);
  * Requirements: n_rows >= 0; d > 0, d % 128 == 0; 0 < V < 2^23;
  * (V rounded up to 256) * d / 8 < 2^32; token_chunk >= 0 (0 = 16384; rounded
  * up to a multiple of 256; at most 2^23); workspace of
- * acrl_backward_workspace_size() bytes (packed W, W^T, one chunk of H, H^T
+ * acrl_backward_workspace_size() bytes (packed W above 4096 rows, W^T, one chunk of H, H^T
  * and two bf16 copies of its dZ: about 4 V d + 4 c d + 4 c V bytes for a
  * chunk of c rows; plus at most 512 MiB of fp32 partial products where a
  * product of few output tiles is split along K, and the products' work-queue

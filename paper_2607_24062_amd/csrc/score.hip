@@ -75,7 +75,9 @@ constexpr int kBlockT = 8;
 constexpr int kBlockUnits = 32;
 
 struct ScoreParams {
-  const uint8_t* a;        // packed W (bf16) or Wq (e4m3): [n_vtiles][n_chunks][16 KiB]
+  const uint8_t* a;        // W (bf16) or Wq (e4m3): packed [n_vtiles][n_chunks][16 KiB], or row-major [V][64 n_chunks]
+  uint32_t a_pitch;        // bytes between a tile's rows: kChunk (packed) or 64 n_chunks (row-major)
+  uint32_t a_kstep;        // bytes between a row's chunks: kPackBlock (packed) or kChunk (row-major)
   const uint8_t* b;        // packed H or Hq: [n_ttiles][n_chunks][16 KiB]
   int n_chunks;            // bytes per row / kChunk
   int V;
@@ -310,7 +312,8 @@ struct Pipe {
 // strip states do not depend on it.
 // PERSIST: one workgroup per CU claims units from per-XCD queues (below);
 // otherwise one workgroup per unit.
-template <int MODE, int EPI, int NW, int JT, bool PERSIST>
+// ROWMAJOR_A: W may be row-major (p.a_pitch); the packed images only, else.
+template <int MODE, int EPI, int NW, int JT, bool PERSIST, bool ROWMAJOR_A>
 __global__ __attribute__((amdgpu_flat_work_group_size(NW * 64, NW * 64), amdgpu_waves_per_eu(NW / 4, NW / 4)))
 void score_kernel(ScoreParams p) {
   static_assert(NW == 4 || NW == 8, "4 or 8 waves");
@@ -428,6 +431,12 @@ void score_kernel(ScoreParams p) {
   // W / H hold copies of its last row.
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t lane_off = (uint32_t)lane * 16;
+  // the W rows' piece of lane l in a 1 KiB load: row l / 4 of 16, position l % 4
+  // of its 64 bytes, which holds 16-byte column (l % 4) ^ ((row / 4) % 4); a
+  // row-major W is read there
+  const bool a_packed = !ROWMAJOR_A || p.a_pitch == (uint32_t)kChunk;
+  const uint32_t a_row = (uint32_t)lane >> 2;
+  const uint32_t a_col = (((uint32_t)lane & 3) ^ (a_packed ? 0u : ((uint32_t)lane >> 4) & 3u)) * 16;
   const uint32_t tile_bytes = (uint32_t)p.n_chunks * kPackBlock;  // packed bytes of one tile
   const int ptile = t0 / kTileT;                      // packed tile of the tokens
   const uint32_t b_sub = (uint32_t)(t0 % kTileT);      // and their first row in it
@@ -441,15 +450,23 @@ void score_kernel(ScoreParams p) {
   auto issue_chunk = [&](int q, int kc, int stg) {  // chunk kc of the strip's tile q into stage stg
     const int v0 = (vt_begin + q) * kTileV;
     const int a_rows = min(kTileV, p.V - v0);  // valid rows of the vocabulary tile
+    const uint32_t a_last = a_packed ? kTileV - 1 : (uint32_t)a_rows - 1;  // (the image repeats the last row)
     const __amdgpu_buffer_rsrc_t rsrc_a = make_rsrc(p.a + (int64_t)(vt_begin + q) * tile_bytes, tile_bytes);
     if constexpr (EPI == kEpiStore) kc += kc0;
-    const uint32_t soff = (uint32_t)kc * kPackBlock + (uint32_t)wave_u * (kPackBlock / NW);
     uint8_t* la = stage_at(stg) + wave_u * (kPackBlock / NW);
     constexpr int kBWave = TT * kChunk / NW;  // bytes of the token tile per wave
     const uint32_t soff_b = (uint32_t)kc * kPackBlock + b_sub * kChunk + (uint32_t)wave_u * kBWave;
     uint8_t* lb = stage_at(stg) + kTileV * kChunk + wave_u * kBWave;
 #pragma unroll
-    for (int k = 0; k < 16 / NW; ++k) buffer_to_lds<16>(rsrc_a, lane_off, soff + k * 1024, la + k * 1024);
+    for (int k = 0; k < 16 / NW; ++k) {
+      if constexpr (ROWMAJOR_A) {
+        const uint32_t row = min(a_row + (uint32_t)(wave_u * (kTileV / NW) + 16 * k), a_last);
+        buffer_to_lds<16>(rsrc_a, __umul24(row, p.a_pitch) + a_col, (uint32_t)kc * p.a_kstep, la + k * 1024);
+      } else {
+        const uint32_t soff_a = (uint32_t)kc * kPackBlock + (uint32_t)wave_u * (kPackBlock / NW);
+        buffer_to_lds<16>(rsrc_a, lane_off, soff_a + k * 1024, la + k * 1024);
+      }
+    }
 #pragma unroll
     for (int k = 0; k < kBWave / 1024; ++k) buffer_to_lds<16>(rsrc_b, lane_off, soff_b + k * 1024, lb + k * 1024);
     if constexpr (MODE == kFP8Row) {
@@ -1223,15 +1240,28 @@ void launch_tile(unsigned grid, const ScoreParams& p, hipStream_t s) {
   constexpr bool kPersist = (EPI == kEpiSoftmax || EPI == kEpiSample || EPI == kEpiSoftmaxZ || EPI == kEpiSoftmaxDiv ||
                              EPI == kEpiStore) &&
                             !(MODE == kFP8Row && EPI == kEpiSoftmaxZ);
-  if constexpr (kPersist) {
-    ScoreParams q = p;
-    q.units_per_xcd = (int)(grid / kXcds);
-    const unsigned wgs = std::min<unsigned>(grid, (unsigned)device_cus() / kXcds * kXcds);
-    if (wgs < grid) hipLaunchKernelGGL(clear_queue_kernel, dim3(1), dim3(kXcds), 0, s, q.queue);
-    hipLaunchKernelGGL((score_kernel<MODE, EPI, NW, JT, true>), dim3(wgs), dim3(NW * 64), 0, s, q);
-  } else {
-    hipLaunchKernelGGL((score_kernel<MODE, EPI, NW, JT, false>), dim3(grid), dim3(NW * 64), 0, s, p);
-  }
+  // the measures' passes spill more with the row-major addressing in them (92
+  // instead of 40 bytes per lane; 2900 rows, d = 2048: 3.14 against 3.03 ms),
+  // so they have a copy for each; the products' operands are always packed;
+  // the others run packed images as fast either way
+  constexpr bool kOwnCopy = EPI == kEpiSoftmaxZ || EPI == kEpiSoftmaxDiv;
+  auto launch = [&](auto rowmajor_tag) {
+    constexpr bool kRowMajor = decltype(rowmajor_tag)::value;
+    if constexpr (kPersist) {
+      ScoreParams q = p;
+      q.units_per_xcd = (int)(grid / kXcds);
+      const unsigned wgs = std::min<unsigned>(grid, (unsigned)device_cus() / kXcds * kXcds);
+      if (wgs < grid) hipLaunchKernelGGL(clear_queue_kernel, dim3(1), dim3(kXcds), 0, s, q.queue);
+      hipLaunchKernelGGL((score_kernel<MODE, EPI, NW, JT, true, kRowMajor>), dim3(wgs), dim3(NW * 64), 0, s, q);
+    } else {
+      hipLaunchKernelGGL((score_kernel<MODE, EPI, NW, JT, false, kRowMajor>), dim3(grid), dim3(NW * 64), 0, s, p);
+    }
+  };
+  if constexpr (EPI == kEpiStore) launch(std::false_type{});
+  else if constexpr (kOwnCopy) {
+    if (p.a_pitch == (uint32_t)kChunk) launch(std::false_type{});
+    else launch(std::true_type{});
+  } else launch(std::true_type{});
 }
 
 // tile_t: tokens per workgroup tile (plan_score); the narrow ones exist for
@@ -1649,6 +1679,28 @@ Raster raster_blocks(int n_ttiles, int n_strips) {
   return r;
 }
 
+// Calls of at most this many rows read a W that the caller did not pack where
+// it lies, row-major: a 1 KiB load then takes half a 128-byte line of 16 rows
+// and the other half comes from L2 with the next chunk, which costs the
+// kernels 2-4 % (16384 rows, d = 4096: pi 16.95 against 16.45 ms, mu 8.15
+// against 8.0), while the packed copy costs three passes over W (0.49 and
+// 0.24 ms): 1017 rows, d = 4096, pi 2.01 -> 1.13 ms, mu 1.04 -> 0.56; 64 rows
+// 0.72 -> 0.25 and 0.37 -> 0.14 ms; even at about 15000 rows.  The backward's
+// 4-wave dZ pass loses ~8 %, so its line is lower: 1017 rows, d = 4096,
+// 5.03 -> 4.55 ms; 4096 rows, d = 2048, 7.44 -> 7.31 ms; 10111 rows 16.9 ->
+// 17.2 ms.  (The row offset is a 24-bit product.)
+constexpr int64_t kReadInPlaceRows = 12288, kBackwardInPlaceRows = 4096;
+static bool read_in_place(int64_t n_rows, int64_t d, int64_t most) {
+  return n_rows <= most && 2 * d < ((int64_t)1 << 24);
+}
+
+// A operand: packed images, or the row-major matrix itself.
+static void set_a(ScoreParams& p, const void* a, bool packed) {
+  p.a = static_cast<const uint8_t*>(a);
+  p.a_pitch = packed ? (uint32_t)kChunk : (uint32_t)p.n_chunks * kChunk;
+  p.a_kstep = packed ? (uint32_t)kPackBlock : (uint32_t)kChunk;
+}
+
 static void set_raster(ScoreParams& p, const Raster& r) {
   p.n_tblocks = r.n_tblocks;
   p.block_t = r.block_t;
@@ -1726,14 +1778,15 @@ ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows, boo
   // sampling: the strips' best Gumbel key, its logit and row
   pl.ws_best_offset = off;
   off += 3 * align_up(strip_rows * sizeof(float), 256);
-  // packed operands: W, H (2d bytes per row), Wq, Hq (d bytes per row);
-  // the weight images (W, Wq and Wq's MX scales) only when they do not come
-  // prepacked by the caller
+  // packed operands: W, H (2d bytes per row), Wq, Hq (d bytes per row); the
+  // weight images only when they do not come prepacked by the caller and the
+  // rows are too many to read W and Wq in place
+  pl.pack_w = !prepacked && !read_in_place(n_rows, d, kReadInPlaceRows);
   const size_t vrows = (size_t)pl.n_vtiles * kTileV, trows = (size_t)pl.n_ptiles * kTileT;
   const size_t pack_bytes[4] = {vrows * 2 * (size_t)d, trows * 2 * (size_t)d, vrows * (size_t)d, trows * (size_t)d};
   for (int q = 0; q < 4; ++q) {
     pl.ws_pack_offset[q] = off;
-    if (!(prepacked && (q == 0 || q == 2))) off += align_up(pack_bytes[q], 256);
+    if (pl.pack_w || q == 1 || q == 3) off += align_up(pack_bytes[q], 256);
   }
   // MX: packed E8M0 scale images of Wq and Hq (d/32 bytes per row)
   const size_t mx_bytes[2] = {vrows * (size_t)(d / 32), trows * (size_t)(d / 32)};
@@ -1790,14 +1843,13 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
   const uint8_t* pw = static_cast<const uint8_t*>(dsc.packed_weights);
   const PackedWeightsLayout pwl = packed_weights_layout(dsc.V, dsc.d, dsc.mu_scaling);
 
-  // operands -> packed images in the workspace (the weight images only when
-  // the caller did not pass them prepacked)
+  // operands -> packed images in the workspace
   const void* srcs[4] = {dsc.w, dsc.h, dsc.wq, dsc.hq};
   const int64_t src_rows[4] = {dsc.V, dsc.n_rows, dsc.V, dsc.n_rows};
   const int64_t src_tiles[4] = {pl.n_vtiles, pl.n_ptiles, pl.n_vtiles, pl.n_ptiles};
   for (int q = 0; q < 4; ++q) {
     if (!(q < 2 ? do_pi : do_mu)) continue;
-    if (pw && (q == 0 || q == 2)) continue;
+    if (!pl.pack_w && (q == 0 || q == 2)) continue;
     const int64_t row_bytes = q < 2 ? 2 * dsc.d : dsc.d;
     const int64_t units = src_tiles[q] * kTileV * (row_bytes / 16);
     const unsigned blocks = (unsigned)std::min<int64_t>((units + 255) / 256, 8192);
@@ -1806,17 +1858,19 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
   }
 
   // pi: bf16 operands
-  pp.a = pw ? pw + pwl.w_offset : ws + pl.ws_pack_offset[0];
   pp.b = ws + pl.ws_pack_offset[1];
   pp.n_chunks = (int)(2 * dsc.d / kChunk);
+  const void* w_at = pw ? pw + pwl.w_offset : pl.pack_w ? ws + pl.ws_pack_offset[0] : dsc.w;
+  const void* wq_at = pw ? pw + pwl.wq_offset : pl.pack_w ? ws + pl.ws_pack_offset[2] : dsc.wq;
+  set_a(pp, w_at, pw || pl.pack_w);
   pp.part = reinterpret_cast<float*>(ws + pl.ws_part_offset[0]);
   pp.logit = reinterpret_cast<float*>(ws + pl.ws_logit_offset[0]);
 
   // mu: e4m3 operands
   ScoreParams pm = pp;
-  pm.a = pw ? pw + pwl.wq_offset : ws + pl.ws_pack_offset[2];
   pm.b = ws + pl.ws_pack_offset[3];
   pm.n_chunks = (int)(dsc.d / kChunk);
+  set_a(pm, wq_at, pw || pl.pack_w);
   pm.part = reinterpret_cast<float*>(ws + pl.ws_part_offset[1]);
   pm.logit = reinterpret_cast<float*>(ws + pl.ws_logit_offset[1]);
   if (dsc.mu_scaling == ACRL_SCALE_MX32) {
@@ -1973,7 +2027,8 @@ BackwardPlan plan_backward(int64_t n_rows, int64_t d, int64_t V, int64_t chunk) 
     off += align_up(bytes, 256);
     return o;
   };
-  pl.off_w = take(vrows * 2 * (size_t)d);                  // W, rows = vocabulary, K = d
+  pl.pack_w = !read_in_place(n_rows, d, kBackwardInPlaceRows);
+  pl.off_w = take(pl.pack_w ? vrows * 2 * (size_t)d : 0);  // W, rows = vocabulary, K = d (many rows: else read in place)
   pl.off_wt = take(drows * vrows * 2);                     // W^T, rows = d, K = vocabulary
   pl.off_h = take(crows * 2 * (size_t)d);                  // H chunk, rows = tokens, K = d
   pl.off_ht = take(drows * crows * 2);                     // H^T chunk, rows = d, K = tokens
@@ -1998,9 +2053,9 @@ static void launch_product(const uint8_t* a, const uint8_t* b, int n_atiles, int
   ScoreParams pc{};
   unsigned grid = 0;
   gemm_grid(n_atiles, n_btiles, ks, pc, grid);
-  pc.a = a;
   pc.b = b;
   pc.n_chunks = n_chunks;
+  set_a(pc, a, true);
   pc.k_slice = ((n_chunks + ks - 1) / ks + 1) / 2 * 2;  // (no slice is empty: 2 ks < kMinSliceChunks)
   pc.n_rows = (int)n_cols;
   pc.V = (int)m_rows;
@@ -2042,7 +2097,8 @@ hipError_t launch_backward(const acrl_backward_desc& dsc, const BackwardPlan& pl
   // W (rows = vocabulary, for the recomputed logits) and W^T (rows = d, for dH), once per call
   {
     const int64_t units = (int64_t)pl.n_vtiles * kTileV * (2 * d / 16);
-    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)std::min<int64_t>((units + 255) / 256, 8192)), dim3(256), 0, s,
+    if (pl.pack_w)
+      hipLaunchKernelGGL(pack_kernel, dim3((unsigned)std::min<int64_t>((units + 255) / 256, 8192)), dim3(256), 0, s,
                        reinterpret_cast<const uint8_t*>(w), (uint32_t)V, (uint32_t)(2 * d), (uint32_t)units, img_w);
     if (dh)
       hipLaunchKernelGGL(pack_t_kernel, dim3((unsigned)((int64_t)pl.n_dtiles * pl.kch_v)), dim3(256), 0, s, w, V, d,
@@ -2063,9 +2119,9 @@ hipError_t launch_backward(const acrl_backward_desc& dsc, const BackwardPlan& pl
     {
       const ScorePlan sp = plan_score(rows, d, V, 0, true, false);
       ScoreParams pg{};
-      pg.a = img_w;
       pg.b = img_h;
       pg.n_chunks = (int)(2 * d / kChunk);
+      set_a(pg, pl.pack_w ? static_cast<const void*>(img_w) : w, pl.pack_w);
       pg.V = (int)V;
       pg.n_rows = (int)rows;
       pg.n_vtiles = sp.n_vtiles;
@@ -2106,7 +2162,7 @@ hipError_t launch_sample(const acrl_sample_desc& dsc, const ScorePlan& pl, hipSt
   const int64_t src_rows[2] = {dsc.V, dsc.n_rows};
   const int64_t src_tiles[2] = {pl.n_vtiles, pl.n_ptiles};
   for (int q = 0; q < 2; ++q) {
-    if (q == 0 && pw) continue;  // Wq comes prepacked
+    if (q == 0 && !pl.pack_w) continue;
     const int64_t units = src_tiles[q] * kTileV * (dsc.d / 16);
     const unsigned blocks = (unsigned)std::min<int64_t>((units + 255) / 256, 8192);
     hipLaunchKernelGGL(pack_kernel, dim3(blocks), dim3(256), 0, s, static_cast<const uint8_t*>(srcs[q]),
@@ -2123,9 +2179,10 @@ hipError_t launch_sample(const acrl_sample_desc& dsc, const ScorePlan& pl, hipSt
   pm.inv_temp = dsc.inv_temperature;
   pm.mx_row_bytes = (int)(dsc.d / 32);
   pm.queue = reinterpret_cast<int*>(ws + pl.ws_queue_offset);
-  pm.a = pw ? pw + pwl.wq_offset : ws + pl.ws_pack_offset[2];
   pm.b = ws + pl.ws_pack_offset[3];
   pm.n_chunks = (int)(dsc.d / kChunk);
+  const void* wq_at = pw ? pw + pwl.wq_offset : pl.pack_w ? ws + pl.ws_pack_offset[2] : dsc.wq;
+  set_a(pm, wq_at, pw || pl.pack_w);
   pm.part = reinterpret_cast<float*>(ws + pl.ws_part_offset[1]);
   pm.seed_lo = (uint32_t)dsc.seed;
   pm.seed_hi = (uint32_t)(dsc.seed >> 32);

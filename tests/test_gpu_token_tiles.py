@@ -71,3 +71,43 @@ def test_workspace_grows_with_rows():
             assert L.acrl_score_workspace_query(ctypes.byref(desc), ctypes.byref(nb)) == 0
             assert nb.value >= last, (d, V, n)
             last = nb.value
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scaling", [oracle.PER_TENSOR, oracle.PER_ROW, oracle.MX32])
+@pytest.mark.parametrize("T,V", [(1, 100), (130, 300), (700, 1000), (12288, 300), (12289, 300)])
+def test_weights_read_in_place_equal_packed(scaling, T, V):
+    """W and Wq read where they lie (up to 12288 rows), packed by the call
+    (above) and packed by the caller: the same bits everywhere."""
+    torch, dev = torch_dev()
+    from paper_2607_24062_amd import acrl
+    h, w = up_bf16(torch, dev, random_bf16((T, 256), 31)), up_bf16(torch, dev, random_bf16((V, 256), 32, std=0.2))
+    idt = up(torch, dev, np.random.default_rng(33).integers(0, V, size=T).astype(np.int32))
+    hq, hs = acrl.acrl_quantize_fp8(h, scaling)
+    wq, ws = acrl.acrl_quantize_fp8(w, scaling)
+    packed = acrl.acrl_pack_weights(w, wq, ws, scaling)
+    res = []
+    for pw in (None, packed):
+        out = acrl.acrl_score_pi_mu(h, w, hq, hs, wq, ws, scaling, idt, packed_weights=pw)
+        div = acrl.acrl_score_pi_mu(h, w, hq, hs, wq, ws, scaling, idt, packed_weights=pw, divergence=True)
+        draw, lm = acrl.acrl_sample_mu(hq, hs, wq, ws, scaling, seed=5, packed_weights=pw)
+        out.update({"div_" + k: v for k, v in div.items()}, draw=draw, lm=lm)
+        res.append({k: down(v) for k, v in out.items()})
+    for k in res[0]:
+        assert np.array_equal(res[0][k], res[1][k], equal_nan=True), k  # (l2 may be NaN: its terms cancel)
+
+
+@pytest.mark.gpu
+def test_backward_weights_read_in_place_equal_packed():
+    torch, dev = torch_dev()
+    from paper_2607_24062_amd import acrl
+    T, V, d = 4097, 1000, 256
+    h, w = up_bf16(torch, dev, random_bf16((T, d), 41)), up_bf16(torch, dev, random_bf16((V, d), 42, std=0.2))
+    r = np.random.default_rng(43)
+    ids = up(torch, dev, r.integers(0, V, size=T).astype(np.int32))
+    coef = up(torch, dev, r.normal(0, 1e-2, size=T).astype(np.float32))
+    lse = up(torch, dev, np.full(T, 8.0, np.float32))  # any lse: the same recomputed probabilities on both paths
+    a, _ = acrl.acrl_lm_head_backward(h, w, ids, coef, lse, want_dw=False)          # packs W
+    b, _ = acrl.acrl_lm_head_backward(h[:-1], w, ids[:-1], coef[:-1], lse[:-1], want_dw=False)  # reads it in place
+    torch.cuda.synchronize()
+    assert np.array_equal(down(a)[:-1], down(b))
