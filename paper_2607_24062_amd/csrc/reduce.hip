@@ -16,6 +16,7 @@
 // results are deterministic (no floating-point atomics).  These kernels are
 // HBM / latency bound; the controller is a plain grid-stride stream.
 #include <mutex>
+#include <type_traits>
 
 #include "acrl_internal.h"
 
@@ -30,27 +31,74 @@ struct SeqRec {
   double pad;
 };
 
-__device__ __forceinline__ double block_sum(double v, double* sh) {
-  v = wave_sum(v);
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
-  __syncthreads();
-  double t = 0.0;
-  for (int k = 0; k < (int)(blockDim.x >> 6); ++k) t += sh[k];
-  return t;
+// Sum / maximum over groups of N = 4, 16 or 64 consecutive lanes: DPP inside
+// each row of 16, lane exchanges across rows.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <int N>
+__device__ __forceinline__ double lane_sum(double v) {
+  v += dpp_f64<0xB1>(v);                      // quad_perm [1,0,3,2]
+  v += dpp_f64<0x4E>(v);                      // quad_perm [2,3,0,1]
+  if constexpr (N >= 16) {
+    v += dpp_f64<0x124>(v);                   // row_ror:4
+    v += dpp_f64<0x128>(v);                   // row_ror:8
+  }
+  if constexpr (N == 64) {
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+  }
+  return v;
+}
+template <int N>
+__device__ __forceinline__ double lane_max(double v) {
+  v = fmax(v, dpp_f64<0xB1>(v));
+  v = fmax(v, dpp_f64<0x4E>(v));
+  if constexpr (N >= 16) {
+    v = fmax(v, dpp_f64<0x124>(v));
+    v = fmax(v, dpp_f64<0x128>(v));
+  }
+  if constexpr (N == 64) {
+    v = fmax(v, __shfl_xor(v, 16));
+    v = fmax(v, __shfl_xor(v, 32));
+  }
+  return v;
 }
 
-__device__ __forceinline__ double block_max(double v, double* sh) {
+// Sums of NS values and the maximum of mx over a workgroup of NT = 64, 256 or
+// 1024 threads, one barrier (none for a wavefront): trees inside each
+// wavefront, then every thread's lane group of NT / 64 lanes takes one
+// wavefront's result each and adds them by the same tree.  Deterministic.
+// (The serial sum over the wavefronts, one dependent LDS read after another,
+// made the 1024-thread batch statistics 13.5 us long.)
+template <int NS, int NT>
+struct BlockShared {
+  double s[NT / 64][NS];
+  double mx[NT / 64];
+};
+template <int NS, int NT>
+__device__ __forceinline__ void block_stats(double (&v)[NS], double& mx, BlockShared<NS, NT>& sh) {
+  constexpr int NW = NT / 64;
+  static_assert(NW == 1 || NW == 4 || NW == 16, "1, 4 or 16 wavefronts");
 #pragma unroll
-  for (int m = 1; m < 64; m <<= 1) v = fmax(v, __shfl_xor(v, m));
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
-  __syncthreads();
-  double t = sh[0];
-  for (int k = 1; k < (int)(blockDim.x >> 6); ++k) t = fmax(t, sh[k]);
-  return t;
+  for (int k = 0; k < NS; ++k) v[k] = lane_sum<64>(v[k]);
+  mx = lane_max<64>(mx);
+  if constexpr (NW > 1) {
+    const int w = threadIdx.x >> 6, q = threadIdx.x & (NW - 1);
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+      for (int k = 0; k < NS; ++k) sh.s[w][k] = v[k];
+      sh.mx[w] = mx;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NS; ++k) v[k] = lane_sum<NW>(sh.s[q][k]);
+    mx = lane_max<NW>(sh.mx[q]);
+  }
 }
 
 // Count, mean and sum of squared deviations of a set of values; two sets
@@ -66,121 +114,95 @@ __device__ __forceinline__ Var var_merge(const Var& a, const Var& b) {
   return Var{n, a.mu + d * f, a.m2 + b.m2 + d * d * a.n * f};
 }
 
-// Block-wide sums of NS values, their maximum and the merge of the threads'
-// Vars, with one barrier: shuffle trees inside each wavefront, then every
-// thread combines the wavefronts' results in wavefront order, so all threads
-// hold the (deterministic) totals.  A second call on the same shared memory
-// needs a barrier in between.
-template <int NS, int NT = kRedThreads>
-struct BlockShared {
-  double s[NT / 64][NS];
-  double mx[NT / 64];
-  Var var[NT / 64];
-};
-template <int NS, int NT = kRedThreads>
-__device__ __forceinline__ void block_stats(double (&v)[NS], double& mx, Var& var, BlockShared<NS, NT>& sh) {
-  const int w = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < NS; ++k) v[k] = wave_sum(v[k]);
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    mx = fmax(mx, __shfl_xor(mx, m));
-    var = var_merge(var, Var{__shfl_xor(var.n, m), __shfl_xor(var.mu, m), __shfl_xor(var.m2, m)});
-  }
-  if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-    for (int k = 0; k < NS; ++k) sh.s[w][k] = v[k];
-    sh.mx[w] = mx;
-    sh.var[w] = var;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    double t = 0.0;
-#pragma unroll 1
-    for (int q = 0; q < NT / 64; ++q) t += sh.s[q][k];
-    v[k] = t;
-  }
-  mx = sh.mx[0];
-  var = sh.var[0];
-#pragma unroll 1
-  for (int q = 1; q < NT / 64; ++q) {
-    mx = fmax(mx, sh.mx[q]);
-    var = var_merge(var, sh.var[q]);
-  }
+// A thread's (n, mu, m2) as its share of the sum of squared deviations about
+// the mean of all threads' values: m2 + n (mu - mean)^2.  The shares add up to
+// the whole set's, so the threads combine by sums, without the pairwise
+// update's division at each level of a tree.
+__device__ __forceinline__ double var_about(const Var& v, double mean) {
+  const double d = v.mu - mean;
+  return v.n > 0.0 ? fma(v.n * d, d, v.m2) : 0.0;
 }
 
 __device__ __forceinline__ double token_distance(float lp_pi, float lp_mu) {
   return fabs(exp((double)lp_pi) - exp((double)lp_mu));
 }
 
-// VEC consecutive slots of one thread: 16-byte loads for VEC = 4.
-template <int VEC>
-struct Slots {
-  float a[VEC], b[VEC], hp[VEC], hm[VEC];
-  uint8_t m[VEC];
-};
-template <int VEC>
-__device__ __forceinline__ void load_slots(const acrl_reduce_desc& p, int64_t t, bool ent, Slots<VEC>& v) {
-  if constexpr (VEC == 4) {
-    const float4 a = *reinterpret_cast<const float4*>(p.logp_pi + t);
-    const float4 b = *reinterpret_cast<const float4*>(p.logp_mu + t);
-    const uchar4 m = *reinterpret_cast<const uchar4*>(p.mask + t);
-    v.a[0] = a.x; v.a[1] = a.y; v.a[2] = a.z; v.a[3] = a.w;
-    v.b[0] = b.x; v.b[1] = b.y; v.b[2] = b.z; v.b[3] = b.w;
-    v.m[0] = m.x; v.m[1] = m.y; v.m[2] = m.z; v.m[3] = m.w;
-    if (ent) {
-      const float4 hp = p.entropy_pi ? *reinterpret_cast<const float4*>(p.entropy_pi + t) : float4{};
-      const float4 hm = p.entropy_mu ? *reinterpret_cast<const float4*>(p.entropy_mu + t) : float4{};
-      v.hp[0] = hp.x; v.hp[1] = hp.y; v.hp[2] = hp.z; v.hp[3] = hp.w;
-      v.hm[0] = hm.x; v.hm[1] = hm.y; v.hm[2] = hm.z; v.hm[3] = hm.w;
-    }
+// Workgroup size of the per-response kernels and the slots of a thread: four
+// per round, consecutive (VEC: 16-byte loads, responses whose slots start
+// 16-byte aligned) or NT apart.  64 threads take a response of up to 256
+// slots in one round.  Longer ones take 1024 threads while that leaves no
+// more than one workgroup per CU, 256 otherwise.
+constexpr int kSlots = 4;
+inline int seq_threads(int64_t B, int64_t L) {
+  if (L <= 64 * kSlots) return 64;
+  return L > kRedThreads * kSlots && B <= 256 ? 1024 : kRedThreads;
+}
+template <int NT, bool VEC>
+__device__ __forceinline__ int64_t first_slot() {
+  return VEC ? (int64_t)threadIdx.x * kSlots : (int64_t)threadIdx.x;
+}
+// The mask of the thread's slots from slot j on of the response at `base`
+// (slots past L: 0) and four values of x there, 0 past L.
+template <int NT, bool VEC>
+__device__ __forceinline__ void load_mask(const uint8_t* __restrict__ mask, int64_t base, int64_t j, int64_t L,
+                                          uint8_t (&m)[kSlots]) {
+  if constexpr (VEC) {
+    const uchar4 t = *reinterpret_cast<const uchar4*>(mask + base + j);
+    m[0] = t.x; m[1] = t.y; m[2] = t.z; m[3] = t.w;
   } else {
-    v.a[0] = p.logp_pi[t];
-    v.b[0] = p.logp_mu[t];
-    v.m[0] = p.mask[t];
-    if (ent) {
-      v.hp[0] = p.entropy_pi ? p.entropy_pi[t] : 0.0f;
-      v.hm[0] = p.entropy_mu ? p.entropy_mu[t] : 0.0f;
-    }
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) m[k] = j + k * NT < L ? mask[base + j + k * NT] : (uint8_t)0;
+  }
+}
+template <int NT, bool VEC>
+__device__ __forceinline__ void load_slots(const float* __restrict__ x, int64_t base, int64_t j, int64_t L,
+                                           float (&v)[kSlots]) {
+  if constexpr (VEC) {
+    const float4 t = *reinterpret_cast<const float4*>(x + base + j);
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+  } else {
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) v[k] = j + k * NT < L ? x[base + j + k * NT] : 0.0f;
   }
 }
 
-// One workgroup per response; thread k takes the VEC-slot pieces k, k + 256,
-// ... of the response's L slots.  Every slot is loaded (masked ones too: no
-// load waits on the mask).  The sums are plain fp64 sums in piece order; the
-// squared deviations of each piece (about its own mean) merge into the
-// thread's running Var, and the threads' Vars merge in a fixed tree.
-template <int VEC>
-__global__ __launch_bounds__(kRedThreads) void reduce_seq_kernel(acrl_reduce_desc p, SeqRec* rec,
-                                                                 uint32_t* unsorted) {
-  __shared__ BlockShared<5> sh;
+// One workgroup per response.  Every slot is loaded (masked ones too: no load
+// waits on the mask).  The sums are plain fp64 sums in slot order; the squared
+// deviations of each round's four slots (about their own mean) merge into the
+// thread's running Var.  Latency bound: 64 responses of 4096 slots 9.8 us with
+// 256 threads (four rounds of exponentials and divisions), 7.0 with 1024; 4 of
+// 64 slots 5.6 us with 256 threads, 3.4 with 64.
+template <int NT, bool VEC>
+__global__ __launch_bounds__(NT) void reduce_seq_kernel(acrl_reduce_desc p, SeqRec* rec, uint32_t* unsorted) {
+  __shared__ BlockShared<5, NT> sh;
+  __shared__ BlockShared<1, NT> sh2;
   const int64_t i = blockIdx.x;
   const int64_t base = i * p.L;
-  const bool ent = p.entropy_pi || p.entropy_mu;
-  constexpr int kStride = kRedThreads * VEC;
-  double n = 0, sd = 0, sl = 0, shp = 0, shm = 0, mx = 0;
+  double v[5] = {0, 0, 0, 0, 0};  // n, sum d, sum log-ratio, sum H_pi, sum H_mu
+  double mx = 0;
   Var var{0.0, 0.0, 0.0};
-#pragma unroll 2
-  for (int64_t j = (int64_t)threadIdx.x * VEC; j < p.L; j += kStride) {
-    Slots<VEC> v;
-    load_slots<VEC>(p, base + j, ent, v);
-    double dv[VEC];
-    float dt[VEC];
+  for (int64_t j = first_slot<NT, VEC>(); j < p.L; j += NT * kSlots) {
+    uint8_t m[kSlots];
+    float a[kSlots], b[kSlots], hp[kSlots] = {}, hm[kSlots] = {};
+    load_mask<NT, VEC>(p.mask, base, j, p.L, m);
+    load_slots<NT, VEC>(p.logp_pi, base, j, p.L, a);
+    load_slots<NT, VEC>(p.logp_mu, base, j, p.L, b);
+    if (p.entropy_pi) load_slots<NT, VEC>(p.entropy_pi, base, j, p.L, hp);
+    if (p.entropy_mu) load_slots<NT, VEC>(p.entropy_mu, base, j, p.L, hm);
+    double dv[kSlots];
+    float dt[kSlots];
     double pn = 0.0, ps = 0.0;
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) {
+    for (int k = 0; k < kSlots; ++k) {
       dt[k] = 0.0f;
       dv[k] = 0.0;
-      if (v.m[k]) {
-        dv[k] = token_distance(v.a[k], v.b[k]);
-        n += 1.0;
-        sd += dv[k];
-        sl += (double)v.a[k] - (double)v.b[k];
-        if (ent) {
-          shp += v.hp[k];
-          shm += v.hm[k];
-        }
+      if (m[k]) {
+        dv[k] = token_distance(a[k], b[k]);
+        v[0] += 1.0;
+        v[1] += dv[k];
+        v[2] += (double)a[k] - (double)b[k];
+        v[3] += hp[k];
+        v[4] += hm[k];
         mx = fmax(mx, dv[k]);
         dt[k] = (float)dv[k];
         pn += 1.0;
@@ -191,33 +213,35 @@ __global__ __launch_bounds__(kRedThreads) void reduce_seq_kernel(acrl_reduce_des
       const double pm = ps / pn;
       double pm2 = 0.0;
 #pragma unroll
-      for (int k = 0; k < VEC; ++k)
-        if (v.m[k]) pm2 += (dv[k] - pm) * (dv[k] - pm);
+      for (int k = 0; k < kSlots; ++k)
+        if (m[k]) pm2 += (dv[k] - pm) * (dv[k] - pm);
       var = var_merge(var, Var{pn, pm, pm2});
     }
     if (p.d_tok) {
-      if constexpr (VEC == 4) *reinterpret_cast<float4*>(p.d_tok + base + j) = make_float4(dt[0], dt[1], dt[2], dt[3]);
-      else p.d_tok[base + j] = dt[0];
+      if constexpr (VEC) {
+        *reinterpret_cast<float4*>(p.d_tok + base + j) = make_float4(dt[0], dt[1], dt[2], dt[3]);
+      } else {
+#pragma unroll
+        for (int k = 0; k < kSlots; ++k)
+          if (j + k * NT < p.L) p.d_tok[base + j + k * NT] = dt[k];
+      }
     }
   }
-  double v[5] = {n, sd, sl, shp, shm};
-  block_stats<5>(v, mx, var, sh);
-  n = v[0];
-  sd = v[1];
-  sl = v[2];
-  shp = v[3];
-  shm = v[4];
+  block_stats<5, NT>(v, mx, sh);
+  const double mean = v[0] > 0 ? v[1] / v[0] : 0.0;
+  double m2[1] = {var_about(var, mean)}, unused = 0.0;
+  block_stats<1, NT>(m2, unused, sh2);
   if (threadIdx.x == 0) {
-    const double mean = n > 0 ? sd / n : 0.0;
     SeqRec r;
-    r.n = n; r.sum_d = sd; r.sum_lr = sl; r.sum_hp = shp; r.sum_hm = shm; r.max_d = mx; r.m2 = var.m2;
+    r.n = v[0]; r.sum_d = v[1]; r.sum_lr = v[2]; r.sum_hp = v[3]; r.sum_hm = v[4]; r.max_d = mx; r.m2 = m2[0];
     r.pad = 0;
     rec[i] = r;
-    if (p.seq_len) p.seq_len[i] = (int32_t)n;
-    if (p.seq_sum_d) p.seq_sum_d[i] = sd;
-    if (p.seq_sum_logratio) p.seq_sum_logratio[i] = sl;
+    if (p.seq_len) p.seq_len[i] = (int32_t)v[0];
+    if (p.seq_sum_d) p.seq_sum_d[i] = v[1];
+    if (p.seq_sum_logratio) p.seq_sum_logratio[i] = v[2];
     p.seq_mean_d[i] = (float)mean;
-    if (i + 1 < p.B && p.group_of_seq[i] > p.group_of_seq[i + 1]) atomicOr(unsorted, 1u);
+    // (no flag: one workgroup does all groups, in whatever order they come)
+    if (unsorted && i + 1 < p.B && p.group_of_seq[i] > p.group_of_seq[i + 1]) atomicOr(unsorted, 1u);
   }
 }
 
@@ -226,18 +250,53 @@ __global__ void clear_flag_kernel(uint32_t* f) { *f = 0u; }
 // Per-group partial record (the groups partition the responses, so the
 // batch statistics come from these).
 struct GroupRec {
-  double n, sum_d, sum_lr, sum_hp, sum_hm, max_d, nseq, mu, m2;
-  double pad[7];
+  double n, sum_d, sum_lr, sum_hp, sum_hm, max_d, nseq, mu, m2, y;
 };
+static_assert(sizeof(GroupRec) <= 128, "the workspace reserves 128 bytes");
+
+// Sums over the responses of one group that a thread takes.
+struct GroupSums {
+  double v[7] = {0, 0, 0, 0, 0, 0, 0};  // sum of means, responses, n, sum d, sum log-ratio, sum H_pi, sum H_mu
+  double mx = 0.0;
+  Var var{0.0, 0.0, 0.0};
+  __device__ __forceinline__ void add(const SeqRec& r) {
+    if (r.n > 0) {
+      const double mean = r.sum_d / r.n;
+      v[0] += mean;
+      v[1] += 1.0;
+      v[2] += r.n;
+      v[3] += r.sum_d;
+      v[4] += r.sum_lr;
+      v[5] += r.sum_hp;
+      v[6] += r.sum_hm;
+      mx = fmax(mx, r.max_d);
+      var = var_merge(var, Var{r.n, mean, r.m2});
+    }
+  }
+};
+
+// Group g's outputs and record from its sums (mu, m2: its tokens' mean d and
+// squared deviations).
+__device__ __forceinline__ GroupRec store_group(const acrl_reduce_desc& p, int g, const GroupSums& t, double mu,
+                                                double m2) {
+  const double c = t.v[1];
+  const double y = c > 0 ? t.v[0] / c : 0.0;
+  p.group_y[g] = (float)y;
+  if (p.group_nseq) p.group_nseq[g] = (int32_t)c;
+  GroupRec r;
+  r.n = t.v[2]; r.sum_d = t.v[3]; r.sum_lr = t.v[4]; r.sum_hp = t.v[5]; r.sum_hm = t.v[6]; r.max_d = t.mx; r.nseq = c;
+  r.mu = mu; r.m2 = m2; r.y = y;
+  return r;
+}
 
 // One workgroup per group: Y_g over the group's non-empty responses, and the
 // group's share of the batch statistics.  When group_of_seq is non-decreasing
 // (flag unsorted == 0, set by the per-response kernel) the group's responses are
 // the range found by binary search; otherwise every response is scanned.
 __global__ __launch_bounds__(kRedThreads) void reduce_group_kernel(acrl_reduce_desc p, const SeqRec* rec,
-                                                                   const uint32_t* unsorted, double* gy,
-                                                                   double* gcount, GroupRec* grec) {
-  __shared__ BlockShared<7> sh;
+                                                                   const uint32_t* unsorted, GroupRec* grec) {
+  __shared__ BlockShared<7, kRedThreads> sh;
+  __shared__ BlockShared<1, kRedThreads> sh2;
   __shared__ int64_t range[2];
   const int g = blockIdx.x;
   const bool sorted = *unsorted == 0u;
@@ -263,82 +322,100 @@ __global__ __launch_bounds__(kRedThreads) void reduce_group_kernel(acrl_reduce_d
     lo = range[0];
     hi = range[1];
   }
-  double v[7] = {0, 0, 0, 0, 0, 0, 0};  // sum of means, responses, n, sum d, sum log-ratio, sum H_pi, sum H_mu
-  double mx = 0.0;
-  Var var{0.0, 0.0, 0.0};
-  for (int64_t i = lo + threadIdx.x; i < hi; i += kRedThreads) {
-    if (sorted || p.group_of_seq[i] == g) {
-      const SeqRec r = rec[i];
-      if (r.n > 0) {
-        const double mean = r.sum_d / r.n;
-        v[0] += mean;
-        v[1] += 1.0;
-        v[2] += r.n;
-        v[3] += r.sum_d;
-        v[4] += r.sum_lr;
-        v[5] += r.sum_hp;
-        v[6] += r.sum_hm;
-        mx = fmax(mx, r.max_d);
-        var = var_merge(var, Var{r.n, mean, r.m2});
-      }
-    }
-  }
-  block_stats<7>(v, mx, var, sh);
-  if (threadIdx.x == 0) {
-    const double c = v[1];
-    const double y = c > 0 ? v[0] / c : 0.0;
-    gy[g] = y;
-    gcount[g] = c;
-    p.group_y[g] = (float)y;
-    if (p.group_nseq) p.group_nseq[g] = (int32_t)c;
-    GroupRec r;
-    r.n = v[2]; r.sum_d = v[3]; r.sum_lr = v[4]; r.sum_hp = v[5]; r.sum_hm = v[6]; r.max_d = mx; r.nseq = c;
-    r.mu = var.mu; r.m2 = var.m2;
-    for (int k = 0; k < 7; ++k) r.pad[k] = 0.0;
-    grec[g] = r;
-  }
+  GroupSums t;
+  for (int64_t i = lo + threadIdx.x; i < hi; i += kRedThreads)
+    if (sorted || p.group_of_seq[i] == g) t.add(rec[i]);
+  block_stats<7, kRedThreads>(t.v, t.mx, sh);
+  const double mu = t.v[2] > 0 ? t.v[3] / t.v[2] : 0.0;
+  double m2[1] = {var_about(t.var, mu)}, unused = 0.0;
+  block_stats<1, kRedThreads>(m2, unused, sh2);
+  if (threadIdx.x == 0) grec[g] = store_group(p, g, t, mu, m2[0]);
 }
 
-// One workgroup of kBatchThreads: batch statistics from the group records.
-constexpr int kBatchThreads = 1024;
-__global__ __launch_bounds__(kBatchThreads) void reduce_batch_kernel(acrl_reduce_desc p, const GroupRec* grec,
-                                                                     const double* gy, const double* gcount) {
-  __shared__ BlockShared<8, kBatchThreads> sh;
+// Batch statistics from the group records of the workgroup's threads.
+struct BatchSums {
   double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // n, sum d, sum log-ratio, sum H_pi, sum H_mu, responses, sum Y_g, groups
   double mx = 0.0;
   Var var{0.0, 0.0, 0.0};
-  for (int64_t g = threadIdx.x; g < p.n_groups; g += kBatchThreads) {
-    const GroupRec r = grec[g];
+  __device__ __forceinline__ void add(const GroupRec& r) {
     v[0] += r.n;
     v[1] += r.sum_d;
     v[2] += r.sum_lr;
     v[3] += r.sum_hp;
     v[4] += r.sum_hm;
     v[5] += r.nseq;
-    if (gcount[g] > 0) {
-      v[6] += gy[g];
+    if (r.nseq > 0) {
+      v[6] += r.y;
       v[7] += 1.0;
     }
     mx = fmax(mx, r.max_d);
     var = var_merge(var, Var{r.n, r.mu, r.m2});
   }
-  block_stats<8, kBatchThreads>(v, mx, var, sh);
+};
+template <int NT>
+__device__ __forceinline__ void batch_stats(const acrl_reduce_desc& p, BatchSums& t, BlockShared<8, NT>& sh,
+                                            BlockShared<1, NT>& sh2) {
+  block_stats<8, NT>(t.v, t.mx, sh);
+  const double n = t.v[0], ng = t.v[7], mean = n > 0 ? t.v[1] / n : 0.0;
+  double m2[1] = {var_about(t.var, mean)}, unused = 0.0;
+  block_stats<1, NT>(m2, unused, sh2);
   if (threadIdx.x == 0) {
-    const double n = v[0], ng = v[7];
     double* st = p.stats;
-    st[ACRL_STAT_Y_BATCH] = ng > 0 ? v[6] / ng : 0.0;
-    st[ACRL_STAT_TOK_MEAN_D] = n > 0 ? v[1] / n : 0.0;
-    st[ACRL_STAT_TOK_MAX_D] = mx;
-    st[ACRL_STAT_TOK_STD_D] = n > 0 ? sqrt(var.m2 / n) : 0.0;
-    st[ACRL_STAT_MEAN_H_PI] = n > 0 ? v[3] / n : 0.0;
-    st[ACRL_STAT_MEAN_H_MU] = n > 0 ? v[4] / n : 0.0;
+    st[ACRL_STAT_Y_BATCH] = ng > 0 ? t.v[6] / ng : 0.0;
+    st[ACRL_STAT_TOK_MEAN_D] = mean;
+    st[ACRL_STAT_TOK_MAX_D] = t.mx;
+    st[ACRL_STAT_TOK_STD_D] = n > 0 ? sqrt(m2[0] / n) : 0.0;
+    st[ACRL_STAT_MEAN_H_PI] = n > 0 ? t.v[3] / n : 0.0;
+    st[ACRL_STAT_MEAN_H_MU] = n > 0 ? t.v[4] / n : 0.0;
     st[ACRL_STAT_N_TOKENS] = n;
     st[ACRL_STAT_N_GROUPS] = ng;
-    st[ACRL_STAT_TOK_MEAN_LOGRATIO] = n > 0 ? v[2] / n : 0.0;
-    st[ACRL_STAT_N_SEQS] = v[5];
+    st[ACRL_STAT_TOK_MEAN_LOGRATIO] = n > 0 ? t.v[2] / n : 0.0;
+    st[ACRL_STAT_N_SEQS] = t.v[5];
   }
 }
+constexpr int kBatchThreads = 1024;
+__global__ __launch_bounds__(kBatchThreads) void reduce_batch_kernel(acrl_reduce_desc p, const GroupRec* grec) {
+  __shared__ BlockShared<8, kBatchThreads> sh;
+  __shared__ BlockShared<1, kBatchThreads> sh2;
+  BatchSums t;
+  for (int64_t g = threadIdx.x; g < p.n_groups; g += kBatchThreads) t.add(grec[g]);
+  batch_stats<kBatchThreads>(p, t, sh, sh2);
+}
 
+// The groups and the batch in one workgroup, for up to kOneSeqs responses in
+// up to kOneGroups groups: a wavefront takes a group at a time and looks
+// through the responses' groups in LDS, in whatever order they come; the first
+// wavefront then takes one group per lane.  Above, a workgroup per group
+// searches for its range instead (64 groups are four turns of 16 wavefronts).
+// 64 responses in 8 groups: 4.1 us (flag, group and batch launches 1.3 + 5.7 +
+// 13.3 us).
+constexpr int kOneSeqs = 1024, kOneGroups = 64;
+inline bool one_workgroup(int64_t B, int64_t n_groups) { return B <= kOneSeqs && n_groups <= kOneGroups; }
+__global__ __launch_bounds__(1024) void reduce_groups_batch_kernel(acrl_reduce_desc p, const SeqRec* rec) {
+  __shared__ int32_t group_of[kOneSeqs];
+  __shared__ GroupRec grec[kOneGroups];
+  __shared__ BlockShared<8, 64> sh;
+  __shared__ BlockShared<1, 64> sh2;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (threadIdx.x < p.B) group_of[threadIdx.x] = p.group_of_seq[threadIdx.x];
+  __syncthreads();
+  for (int g = w; g < p.n_groups; g += 16) {
+    GroupSums t;
+    for (int i = lane; i < p.B; i += 64)
+      if (group_of[i] == g) t.add(rec[i]);
+#pragma unroll
+    for (int k = 0; k < 7; ++k) t.v[k] = lane_sum<64>(t.v[k]);
+    t.mx = lane_max<64>(t.mx);
+    const double mu = t.v[2] > 0 ? t.v[3] / t.v[2] : 0.0;
+    const double m2 = lane_sum<64>(var_about(t.var, mu));
+    if (lane == 0) grec[g] = store_group(p, g, t, mu, m2);
+  }
+  __syncthreads();
+  if (w != 0) return;
+  BatchSums t;
+  if (lane < p.n_groups) t.add(grec[lane]);
+  batch_stats<64>(p, t, sh, sh2);
+}
 
 // Element-wise controller.  alpha and the weight are evaluated in fp64 from
 // the fp32 inputs (exact conversions), then rounded to fp32 once.  Modes:
@@ -408,72 +485,130 @@ struct SurrSeq {
   double n, J;  // |a_i| and sum_t w_t min(r A, clip(r) A)
 };
 
-// r A, clip(r) A and whether the unclipped term is the minimum (a tie counts
-// as unclipped), in fp64 from the fp32 inputs.
-__device__ __forceinline__ void surr_terms(const acrl_surrogate_desc& p, int64_t t, int64_t i, double& r,
-                                           double& A, double& m, bool& unclipped) {
-  A = p.adv_per_token ? p.adv[t] : p.adv[i];
-  r = exp((double)p.logp_new[t] - (double)p.logp_old[t]);
+// min(r A, clip(r) A), r and whether the unclipped term is the minimum (a tie
+// counts as unclipped), in fp64 from the fp32 inputs.
+__device__ __forceinline__ void surr_terms(const acrl_surrogate_desc& p, double logp_new, double logp_old, double A,
+                                           double& r, double& m, bool& unclipped) {
+  r = exp(logp_new - logp_old);
   const double rc = fmin(fmax(r, 1.0 - (double)p.eps_low), 1.0 + (double)p.eps_high);
   const double u = r * A, c = rc * A;
   unclipped = u <= c;
   m = unclipped ? u : c;
 }
 
-// One workgroup per response.
-__global__ __launch_bounds__(kRedThreads) void surr_seq_kernel(acrl_surrogate_desc p, SurrSeq* rec) {
-  __shared__ double sh[kRedThreads / 64];
+// One workgroup per response (slots as in reduce_seq_kernel: all loaded, no
+// load waits on the mask; 64 responses of 4096 slots 4.6 us, 10.8 one slot at
+// a time behind its mask with 256 threads).
+template <int NT, bool VEC>
+__global__ __launch_bounds__(NT) void surr_seq_kernel(acrl_surrogate_desc p, SurrSeq* rec) {
+  __shared__ BlockShared<2, NT> sh;
   const int64_t i = blockIdx.x;
-  double n = 0, J = 0;
-  for (int64_t j = threadIdx.x; j < p.L; j += kRedThreads) {
-    const int64_t t = i * p.L + j;
-    if (!p.mask[t]) continue;
-    double r, A, m;
-    bool unc;
-    surr_terms(p, t, i, r, A, m, unc);
-    n += 1.0;
-    J += (p.weight ? (double)p.weight[t] : 1.0) * m;
+  const int64_t base = i * p.L;
+  double v[2] = {0, 0}, unused = 0.0;  // n, J
+  for (int64_t j = first_slot<NT, VEC>(); j < p.L; j += NT * kSlots) {
+    uint8_t m[kSlots];
+    float ln[kSlots], lo[kSlots], w[kSlots] = {1.0f, 1.0f, 1.0f, 1.0f}, A[kSlots];
+    load_mask<NT, VEC>(p.mask, base, j, p.L, m);
+    load_slots<NT, VEC>(p.logp_new, base, j, p.L, ln);
+    load_slots<NT, VEC>(p.logp_old, base, j, p.L, lo);
+    if (p.weight) load_slots<NT, VEC>(p.weight, base, j, p.L, w);
+    if (p.adv_per_token) {
+      load_slots<NT, VEC>(p.adv, base, j, p.L, A);
+    } else {
+#pragma unroll
+      for (int k = 0; k < kSlots; ++k) A[k] = p.adv[i];
+    }
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) {
+      if (!m[k]) continue;
+      double r, mn;
+      bool unc;
+      surr_terms(p, ln[k], lo[k], A[k], r, mn, unc);
+      v[0] += 1.0;
+      v[1] += (double)w[k] * mn;
+    }
   }
-  n = block_sum(n, sh);
-  J = block_sum(J, sh);
-  if (threadIdx.x == 0) rec[i] = SurrSeq{n, J};
+  block_stats<2, NT>(v, unused, sh);
+  if (threadIdx.x == 0) rec[i] = SurrSeq{v[0], v[1]};
 }
 
 // One workgroup per group: G_g and the group's sum of per-response means.
 __global__ __launch_bounds__(kRedThreads) void surr_group_kernel(acrl_surrogate_desc p, const SurrSeq* rec,
                                                                  double* gG, double* gJ) {
-  __shared__ double sh[kRedThreads / 64];
+  __shared__ BlockShared<2, kRedThreads> sh;
   const int g = blockIdx.x;
-  double G = 0, J = 0;
+  double v[2] = {0, 0}, unused = 0.0;  // G, J
   for (int64_t i = threadIdx.x; i < p.B; i += kRedThreads)
     if (p.group_of_seq[i] == g && rec[i].n > 0) {
-      G += 1.0;
-      J += rec[i].J / rec[i].n;
+      v[0] += 1.0;
+      v[1] += rec[i].J / rec[i].n;
     }
-  G = block_sum(G, sh);
-  J = block_sum(J, sh);
+  block_stats<2, kRedThreads>(v, unused, sh);
   if (threadIdx.x == 0) {
-    gG[g] = G;
-    gJ[g] = J;
+    gG[g] = v[0];
+    gJ[g] = v[1];
   }
 }
 
-// One workgroup: the number of prompts and the loss.
+// The number of prompts and the loss from a thread's v = {prompts, J}.
+template <int NT>
+__device__ __forceinline__ void surr_loss(const acrl_surrogate_desc& p, double (&v)[2], BlockShared<2, NT>& sh,
+                                          double* prompts) {
+  double unused = 0.0;
+  block_stats<2, NT>(v, unused, sh);
+  if (threadIdx.x == 0) {
+    prompts[0] = v[0];
+    p.loss[0] = v[0] > 0 ? -v[1] / v[0] : 0.0;
+  }
+}
 __global__ __launch_bounds__(kRedThreads) void surr_batch_kernel(acrl_surrogate_desc p, const double* gG,
                                                                  const double* gJ, double* prompts) {
-  __shared__ double sh[kRedThreads / 64];
-  double np = 0, J = 0;
+  __shared__ BlockShared<2, kRedThreads> sh;
+  double v[2] = {0, 0};
   for (int64_t g = threadIdx.x; g < p.n_groups; g += kRedThreads)
     if (gG[g] > 0) {
-      np += 1.0;
-      J += gJ[g] / gG[g];
+      v[0] += 1.0;
+      v[1] += gJ[g] / gG[g];
     }
-  np = block_sum(np, sh);
-  J = block_sum(J, sh);
-  if (threadIdx.x == 0) {
-    prompts[0] = np;
-    p.loss[0] = np > 0 ? -J / np : 0.0;
+  surr_loss<kRedThreads>(p, v, sh, prompts);
+}
+
+// Both in one workgroup (see reduce_groups_batch_kernel): 2.3 us, two launches
+// of 2.2 us each otherwise.
+__global__ __launch_bounds__(1024) void surr_groups_batch_kernel(acrl_surrogate_desc p, const SurrSeq* rec,
+                                                                 double* gG, double* prompts) {
+  __shared__ int32_t group_of[kOneSeqs];
+  __shared__ double G[kOneGroups], J[kOneGroups];
+  __shared__ BlockShared<2, 64> sh;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (threadIdx.x < p.B) group_of[threadIdx.x] = p.group_of_seq[threadIdx.x];
+  __syncthreads();
+  for (int g = w; g < p.n_groups; g += 16) {
+    double n = 0, sum = 0;
+    for (int i = lane; i < p.B; i += 64)
+      if (group_of[i] == g) {
+        const SurrSeq r = rec[i];
+        if (r.n > 0) {
+          n += 1.0;
+          sum += r.J / r.n;
+        }
+      }
+    n = lane_sum<64>(n);
+    sum = lane_sum<64>(sum);
+    if (lane == 0) {
+      G[g] = n;
+      J[g] = sum;
+      gG[g] = n;
+    }
   }
+  __syncthreads();
+  if (w != 0) return;
+  double v[2] = {0, 0};
+  if (lane < p.n_groups && G[lane] > 0) {
+    v[0] = 1.0;
+    v[1] = J[lane] / G[lane];
+  }
+  surr_loss<64>(p, v, sh, prompts);
 }
 
 // Element-wise: coef_t = -w_t r_t A_t / (prompts G_g |a_i|) where the
@@ -490,9 +625,10 @@ __global__ __launch_bounds__(256) void surr_coef_kernel(acrl_surrogate_desc p, c
       if (g < 0 || g >= p.n_groups) {
         out = __builtin_nanf("");
       } else {
-        double r, A, m;
+        const double A = p.adv_per_token ? p.adv[t] : p.adv[i];
+        double r, m;
         bool unc;
-        surr_terms(p, t, i, r, A, m, unc);
+        surr_terms(p, p.logp_new[t], p.logp_old[t], A, r, m, unc);
         if (unc) {
           const double c = 1.0 / (prompts[0] * gG[g] * rec[i].n);
           out = (float)(-c * (p.weight ? (double)p.weight[t] : 1.0) * r * A);
@@ -504,6 +640,21 @@ __global__ __launch_bounds__(256) void surr_coef_kernel(acrl_surrogate_desc p, c
 }
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+inline bool aligned(const void* q, uintptr_t a) { return ((uintptr_t)q & (a - 1)) == 0; }
+
+// launch(workgroup size, 16-byte slots) of a per-response kernel.
+template <typename F>
+inline void launch_seq(int64_t B, int64_t L, bool vec, F&& launch) {
+  auto with = [&](auto nt) {
+    if (vec) launch(nt, std::true_type{});
+    else launch(nt, std::false_type{});
+  };
+  switch (seq_threads(B, L)) {
+    case 64: return with(std::integral_constant<int, 64>{});
+    case 1024: return with(std::integral_constant<int, 1024>{});
+    default: return with(std::integral_constant<int, kRedThreads>{});
+  }
+}
 
 }  // namespace
 
@@ -520,13 +671,23 @@ hipError_t launch_surrogate(const acrl_surrogate_desc& p, hipStream_t s) {
   double* gJ = reinterpret_cast<double*>(ws + off);
   off += align_up((size_t)p.n_groups * sizeof(double), 256);
   double* prompts = reinterpret_cast<double*>(ws + off);
-  if (p.B > 0)
-    hipLaunchKernelGGL(surr_seq_kernel, dim3((unsigned)p.B), dim3(kRedThreads), 0, s, p, rec);
-  if (p.n_groups > 0)
-    hipLaunchKernelGGL(surr_group_kernel, dim3((unsigned)p.n_groups), dim3(kRedThreads), 0, s, p,
-                       (const SurrSeq*)rec, gG, gJ);
-  hipLaunchKernelGGL(surr_batch_kernel, dim3(1), dim3(kRedThreads), 0, s, p, (const double*)gG, (const double*)gJ,
-                     prompts);
+  if (p.B > 0) {
+    const bool vec = p.L % kSlots == 0 && aligned(p.logp_new, 16) && aligned(p.logp_old, 16) && aligned(p.mask, 4) &&
+                     aligned(p.weight, 16) && (!p.adv_per_token || aligned(p.adv, 16));
+    launch_seq(p.B, p.L, vec, [&](auto nt, auto v) {
+      constexpr int NT = decltype(nt)::value;
+      hipLaunchKernelGGL((surr_seq_kernel<NT, decltype(v)::value>), dim3((unsigned)p.B), dim3(NT), 0, s, p, rec);
+    });
+  }
+  if (one_workgroup(p.B, p.n_groups)) {
+    hipLaunchKernelGGL(surr_groups_batch_kernel, dim3(1), dim3(1024), 0, s, p, (const SurrSeq*)rec, gG, prompts);
+  } else {
+    if (p.n_groups > 0)
+      hipLaunchKernelGGL(surr_group_kernel, dim3((unsigned)p.n_groups), dim3(kRedThreads), 0, s, p,
+                         (const SurrSeq*)rec, gG, gJ);
+    hipLaunchKernelGGL(surr_batch_kernel, dim3(1), dim3(kRedThreads), 0, s, p, (const double*)gG, (const double*)gJ,
+                       prompts);
+  }
   const int64_t n = p.B * p.L;
   if (n > 0) {
     int64_t g = (n + 255) / 256;
@@ -539,37 +700,38 @@ hipError_t launch_surrogate(const acrl_surrogate_desc& p, hipStream_t s) {
 
 size_t reduce_workspace_bytes(int64_t B, int64_t L, int64_t n_groups) {
   (void)L;
+  // 144 bytes per group: the bound that the header states for the fixed scratch
   return align_up((size_t)B * sizeof(SeqRec), 256) + 2 * align_up((size_t)n_groups * sizeof(double), 256) +
-         align_up((size_t)n_groups * sizeof(GroupRec), 256) + 256;
+         align_up((size_t)n_groups * 128, 256) + 256;
 }
 
 hipError_t launch_reduce(const acrl_reduce_desc& p, hipStream_t s) {
   uint8_t* ws = static_cast<uint8_t*>(p.workspace);
   SeqRec* rec = reinterpret_cast<SeqRec*>(ws);
   size_t off = align_up((size_t)p.B * sizeof(SeqRec), 256);
-  double* gy = reinterpret_cast<double*>(ws + off);
-  off += align_up((size_t)p.n_groups * sizeof(double), 256);
-  double* gc = reinterpret_cast<double*>(ws + off);
-  off += align_up((size_t)p.n_groups * sizeof(double), 256);
   GroupRec* grec = reinterpret_cast<GroupRec*>(ws + off);
   off += align_up((size_t)p.n_groups * sizeof(GroupRec), 256);
   uint32_t* unsorted = reinterpret_cast<uint32_t*>(ws + off);
-  hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, s, unsorted);
+  const bool one = one_workgroup(p.B, p.n_groups);
+  if (!one) hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, s, unsorted);
   if (p.B > 0) {
     // 16-byte slot loads when every row of slots starts 16-byte aligned
-    auto al = [](const void* q, uintptr_t a) { return ((uintptr_t)q & (a - 1)) == 0; };
-    const bool vec = p.L % 4 == 0 && al(p.logp_pi, 16) && al(p.logp_mu, 16) && al(p.mask, 4) &&
-                     al(p.entropy_pi, 16) && al(p.entropy_mu, 16) && al(p.d_tok, 16);
-    if (vec)
-      hipLaunchKernelGGL(reduce_seq_kernel<4>, dim3((unsigned)p.B), dim3(kRedThreads), 0, s, p, rec, unsorted);
-    else
-      hipLaunchKernelGGL(reduce_seq_kernel<1>, dim3((unsigned)p.B), dim3(kRedThreads), 0, s, p, rec, unsorted);
+    const bool vec = p.L % kSlots == 0 && aligned(p.logp_pi, 16) && aligned(p.logp_mu, 16) && aligned(p.mask, 4) &&
+                     aligned(p.entropy_pi, 16) && aligned(p.entropy_mu, 16) && aligned(p.d_tok, 16);
+    launch_seq(p.B, p.L, vec, [&](auto nt, auto v) {
+      constexpr int NT = decltype(nt)::value;
+      hipLaunchKernelGGL((reduce_seq_kernel<NT, decltype(v)::value>), dim3((unsigned)p.B), dim3(NT), 0, s, p, rec,
+                         one ? nullptr : unsorted);
+    });
   }
-  if (p.n_groups > 0)
-    hipLaunchKernelGGL(reduce_group_kernel, dim3((unsigned)p.n_groups), dim3(kRedThreads), 0, s, p,
-                       (const SeqRec*)rec, (const uint32_t*)unsorted, gy, gc, grec);
-  hipLaunchKernelGGL(reduce_batch_kernel, dim3(1), dim3(kBatchThreads), 0, s, p, (const GroupRec*)grec,
-                     (const double*)gy, (const double*)gc);
+  if (one) {
+    hipLaunchKernelGGL(reduce_groups_batch_kernel, dim3(1), dim3(1024), 0, s, p, (const SeqRec*)rec);
+  } else {
+    if (p.n_groups > 0)
+      hipLaunchKernelGGL(reduce_group_kernel, dim3((unsigned)p.n_groups), dim3(kRedThreads), 0, s, p,
+                         (const SeqRec*)rec, (const uint32_t*)unsorted, grec);
+    hipLaunchKernelGGL(reduce_batch_kernel, dim3(1), dim3(kBatchThreads), 0, s, p, (const GroupRec*)grec);
+  }
   return hipGetLastError();
 }
 
