@@ -1225,8 +1225,11 @@ constexpr int waves_for() {
 // lane, and the measures call ran no faster).  p.queue must point at
 // kXcds * kQueueStride ints of workspace, cleared here.  The backward's
 // plain products run persistent too (8 waves, VGPR accumulators: the q8b
-// backward 502 -> 490 ms, of which ~1 ms from the persistent grid); its dZ
-// pass takes one workgroup per unit (no faster persistent).
+// backward 502 -> 490 ms, of which ~1 ms from the persistent grid), and so
+// does its dZ pass: with one workgroup per unit the XCDs that have a raster
+// block more than others take rounds of units for it alone (1531 rows,
+// d = 4096: 17 blocks, three rounds on one XCD and two on the others, 2.65
+// against 1.93 ms; no difference where every XCD has many blocks).
 inline int device_cus() {
   int dev = 0, n = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -1237,9 +1240,7 @@ inline int device_cus() {
 
 template <int MODE, int EPI, int NW, int JT>
 void launch_tile(unsigned grid, const ScoreParams& p, hipStream_t s) {
-  constexpr bool kPersist = (EPI == kEpiSoftmax || EPI == kEpiSample || EPI == kEpiSoftmaxZ || EPI == kEpiSoftmaxDiv ||
-                             EPI == kEpiStore) &&
-                            !(MODE == kFP8Row && EPI == kEpiSoftmaxZ);
+  constexpr bool kPersist = !(MODE == kFP8Row && EPI == kEpiSoftmaxZ);
   // the measures' passes spill more with the row-major addressing in them (92
   // instead of 40 bytes per lane; 2900 rows, d = 2048: 3.14 against 3.03 ms),
   // so they have a copy for each; the products' operands are always packed;
@@ -2155,6 +2156,7 @@ hipError_t launch_backward(const acrl_backward_desc& dsc, const BackwardPlan& pl
       pg.gz_v = img_zv;
       pg.kch_v = pl.kch_v;
       pg.kch_t = kch_t;
+      pg.queue = reinterpret_cast<int*>(ws + pl.off_queue);
       launch_score_kernel<kBF16, kEpiGrad>((unsigned)sp.raster.grid, pg, s);
     }
     // dH[chunk] = dZ W: A = dZ (rows = tokens), B = W^T (rows = d), K = vocabulary
