@@ -117,7 +117,6 @@ struct ScoreParams {
   int64_t ldc;
   int c_rows;              // valid A rows (M)
   int c_accumulate;        // 1: C += product (C is read once before the K loop)
-  int n_atiles;            // A tiles; strip st is K slice st / n_atiles of A tile st % n_atiles
   int k_slice;             // 64-byte K chunks per slice (even; all of them: one slice)
   int64_t c_slice;         // floats between the slices' products
   // row chunks and the full-vocabulary measures (kEpiSoftmaxZ, kEpiSoftmaxDiv)
@@ -357,11 +356,13 @@ void score_kernel(ScoreParams p) {
   if (tt >= p.n_ttiles || st >= p.n_strips) return;  // padding of the grid
   const int ttg = tt + p.tt_offset;  // token tile in the whole call
   const int t0 = ttg * TT;
-  const int k_part = EPI == kEpiStore ? st / p.n_atiles : 0;  // plain product: the unit's K slice
+  // plain product: the unit's K slice and its strip of A tiles
+  const int a_strips = EPI == kEpiStore ? (p.n_vtiles + p.tiles_per_strip - 1) / p.tiles_per_strip : 1;
+  const int k_part = EPI == kEpiStore ? st / a_strips : 0;
   const int kc0 = EPI == kEpiStore ? k_part * p.k_slice : 0;
   const int n_kc = EPI == kEpiStore ? min(p.k_slice, p.n_chunks - kc0) : p.n_chunks;  // K chunks per tile
-  const int vt_begin = EPI == kEpiStore ? st - k_part * p.n_atiles : st * p.tiles_per_strip;
-  const int vt_end = EPI == kEpiStore ? vt_begin + 1 : min(vt_begin + p.tiles_per_strip, p.n_vtiles);
+  const int vt_begin = (EPI == kEpiStore ? st - k_part * a_strips : st) * p.tiles_per_strip;
+  const int vt_end = min(vt_begin + p.tiles_per_strip, p.n_vtiles);
   const int n_iter = (vt_end - vt_begin) * n_kc;
 
   // ---- per-lane tokens: column r32 of each of the wave's 4 token blocks
@@ -404,7 +405,7 @@ void score_kernel(ScoreParams p) {
 #pragma unroll
     for (int j = 0; j < JT; ++j) acc[b][j] = f32x16{};
   if constexpr (EPI == kEpiStore) {
-    // one output tile per workgroup: start from C when accumulating
+    // start from C when accumulating (one output tile per unit then)
     if (p.c_accumulate) {
       const int m0 = vt_begin * kTileV + wv * 128 + 4 * g;
 #pragma unroll
@@ -945,6 +946,7 @@ void score_kernel(ScoreParams p) {
           const float x = acc[b][j][i];  // (VGPR form: the 8-wave products)
           if (m < p.c_rows && tok[j] < p.n_rows) c[(int64_t)m * p.ldc + tok[j]] = x;
         }
+    wait_vmcnt<0>();  // (as after dZ's stores)
   };
 
   // ---- the pipeline.  Chunks 0..NS-1 are requested up front, one per
@@ -1986,14 +1988,35 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
 }
 
 // ------------------------------------------------------------------ backward
-// Grid of a plain product (kEpiStore): one unit per output tile and K slice,
-// in the scoring kernel's XCD-aware raster (A tiles play the vocabulary
-// strips, B tiles the token tiles).
-static void gemm_grid(int n_atiles, int n_btiles, int n_slices, ScoreParams& pp, unsigned& grid) {
+// Output tiles of a product's unit (of one B tile and consecutive A tiles): the
+// operands of a unit's next tile are on their way while a tile is stored, which
+// counts where K is short, and fewer units fill the last round of the 256 CUs
+// worse.  Times in chunks of one tile: 6 a tile for its stores, 10 a unit for
+// the claim and the pipeline's fill.  dW of d = 4096, V = 151936: 300 rows
+// (16 chunks) 0.97 ms with one tile a unit, 0.89 with 2, 0.875 with 3, 0.885
+// with 4; 1531 rows (48) 1.94, 1.87, 1.89, 1.92; one tile from about 100
+// chunks on.
+static int strip_tiles(int n_atiles, int n_btiles, int n_chunks) {
+  int best = 1;
+  int64_t best_cost = 0;
+  for (int t = 1; t <= 4; ++t) {
+    const int64_t rounds = ((int64_t)((n_atiles + t - 1) / t) * n_btiles + 255) / 256;
+    const int64_t cost = rounds * (t * (n_chunks + 6) + 10);
+    if (t == 1 || cost < best_cost) {
+      best = t;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// Grid of a plain product (kEpiStore): one unit per strip of output tiles and
+// K slice, in the scoring kernel's XCD-aware raster (strips of A tiles play the
+// vocabulary strips, B tiles the token tiles).
+static void gemm_grid(int n_atiles, int n_btiles, int n_slices, int tiles_per_strip, ScoreParams& pp, unsigned& grid) {
   pp.n_vtiles = n_atiles;
-  pp.n_atiles = n_atiles;
-  pp.tiles_per_strip = 1;
-  pp.n_strips = n_atiles * n_slices;
+  pp.tiles_per_strip = tiles_per_strip;
+  pp.n_strips = (n_atiles + tiles_per_strip - 1) / tiles_per_strip * n_slices;
   pp.n_ttiles = n_btiles;
   const Raster r = raster_blocks(n_btiles, pp.n_strips);
   set_raster(pp, r);
@@ -2069,7 +2092,8 @@ static void launch_product(const uint8_t* a, const uint8_t* b, int n_atiles, int
   const int ks = k_slices((int64_t)n_atiles * n_btiles, n_chunks);
   ScoreParams pc{};
   unsigned grid = 0;
-  gemm_grid(n_atiles, n_btiles, ks, pc, grid);
+  const int tps = ks > 1 || accumulate ? 1 : strip_tiles(n_atiles, n_btiles, n_chunks);
+  gemm_grid(n_atiles, n_btiles, ks, tps, pc, grid);
   pc.b = b;
   pc.n_chunks = n_chunks;
   set_a(pc, a, true);

@@ -28,15 +28,17 @@ def test_transposed_images_at_chunk_edges(T, V, d):
     _check_rows(down(dw), rdw, rdwa, "dW")
 
 
-@pytest.mark.parametrize("T", [1531, 1100])  # 6 and 5 token tiles over 594 vocabulary tiles
-def test_dz_units_from_queues(T):
+# 6 and 5 token tiles over 594 vocabulary tiles; dW of 10 and 14 chunks of K in strips of output tiles, the last
+# strip, vocabulary tile and hidden tile partial; with one chunk pair of K
+@pytest.mark.parametrize("T,V,d", [(1531, 151936, 128), (1100, 151936, 128), (300, 65801, 896), (420, 33001, 2176),
+                                   (20, 100001, 640)])
+def test_units_from_queues_and_strips(T, V, d):
     torch, dev = torch_dev()
     from paper_2607_24062_amd import acrl
-    V, d = 151936, 128
     g = torch.Generator(device=dev)
     g.manual_seed(T)
     h = torch.randn((T, d), generator=g, device=dev).bfloat16()
-    w = (torch.randn((V, d), generator=g, device=dev) * 0.2).bfloat16()
+    w = (torch.randn((V, d), generator=g, device=dev) * 2.3 / d ** 0.5).bfloat16()
     ids = torch.randint(0, V, (T,), generator=g, device=dev, dtype=torch.int32)
     coef = torch.randn(T, generator=g, device=dev) / T
     z = h.float() @ w.float().T
