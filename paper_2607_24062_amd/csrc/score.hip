@@ -45,6 +45,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 enum ScoreMode { kBF16 = 0, kFP8Tensor = 1, kFP8Row = 2, kMX = 3 };
 
@@ -876,56 +879,69 @@ void score_kernel(ScoreParams p) {
   // for dW = dZ^T H, in the packed layout pack_kernel writes (16-byte column
   // c of row r at position c ^ ((r/4) % 4) of its 64-byte chunk row).  Rows
   // past V and tokens past n_rows or with coef 0 store 0 (the select also
-  // drops a non-finite p of such a row).
+  // drops a non-finite p of such a row).  Stores go through buffer resources of
+  // one 16 KiB image block each: scalar block addresses and six lane offsets in
+  // all, where 64-bit lane addresses filled the registers (228 VGPRs, and
+  // spills with two waves per SIMD; 150 now).
   auto grad_epilogue = [&](int tile) {
     const int vw = tile * kTileV + wv * 128;  // first vocabulary row of this wave
     const bool odd = (lane & 1) != 0;
-    auto pack2 = [](float lo, float hi) -> uint32_t {
-      return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)lo) |
-             ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)hi) << 16);
-    };
+    // even lanes: low halves of (own, neighbour); odd lanes: high halves of (neighbour, own)
+    const uint32_t pick = odd ? 0x07060302u : 0x01000504u;
+    // the lane's byte offsets in a 16 KiB block of either image, less the
+    // wave's rows: gz_t row r32, column q at t_off ^ 16 q; gz_v row 4 g + odd
+    // (+ 8 (i/4) + i%4: the column's swizzle changes with bit 2 of i)
+    const int wvu = wave_u & 1, wtu = wave_u >> 1;
+    const int t_off = r32 * kChunk + 8 * g + (((r32 >> 2) & 3) << 4);
+    const int v_off = (4 * g + (odd ? 1 : 0)) * kChunk + (((r32 >> 3) ^ g) << 4) + 2 * (r32 & 6);
+    auto run = [&](auto tail_tag) {
+      constexpr bool kTail = decltype(tail_tag)::value;  // rows past V in the tile
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+      for (int b = 0; b < 4; ++b) {
 #pragma unroll
-      for (int j = 0; j < JT; ++j) {
-        float dz[16];
+        for (int j = 0; j < JT; ++j) {
+          // dz = -gc (p - onehot), the token's own row by a branch that few
+          // wavefronts take
+          float dz[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int v = vw + 32 * b + 8 * (i >> 2) + 4 * g + (i & 3);
-          const float pr = fast_exp2(fmaf(acc_read(acc[b][j][i]), c2[j], -gl2[j]));
-          const float oh = v == id[j] ? 1.0f : 0.0f;
-          dz[i] = (v < p.V && gc[j] != 0.0f) ? gc[j] * (oh - pr) : 0.0f;
-        }
-        // rows = tokens: the lane's token row, 4 consecutive vocabulary
-        // values (8 bytes) per 16-byte column q
-        {
-          const int rr = wt * TW + 32 * j + r32;
-          const int kc = tile * 8 + wv * 4 + b;
-          uint8_t* row = p.gz_t + (((int64_t)tt * p.kch_v + kc) * kTileT + rr) * kChunk + 8 * g;
+          for (int i = 0; i < 16; ++i) dz[i] = fast_exp2(fmaf(acc_read(acc[b][j][i]), c2[j], -gl2[j]));
+          const int rel = id[j] - (vw + 32 * b + 4 * g);
+          if ((unsigned)rel < 32u && (rel & 4) == 0) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const uint2 w2 = make_uint2(pack2(dz[4 * q], dz[4 * q + 1]), pack2(dz[4 * q + 2], dz[4 * q + 3]));
-            *reinterpret_cast<uint2*>(row + ((q ^ ((rr >> 2) & 3)) << 4)) = w2;
+            for (int i = 0; i < 16; ++i) dz[i] -= rel == 8 * (i >> 2) + (i & 3) ? 1.0f : 0.0f;
           }
-        }
-        // rows = vocabulary: lanes 2m, 2m+1 hold tokens 2m, 2m+1 of one row;
-        // after one exchange the even lane stores the pair of row i, the odd
-        // lane the pair of row i+1 (4 bytes each)
-        {
-          const int kc = tt * 8 + wt * JT + j;
-          uint8_t* img = p.gz_v + ((int64_t)tile * p.kch_t + kc) * kTileV * kChunk;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const bool valid = gc[j] != 0.0f && (!kTail || vw + 32 * b + 8 * (i >> 2) + 4 * g + (i & 3) < p.V);
+            dz[i] = valid ? -gc[j] * dz[i] : 0.0f;
+          }
+          uint32_t pk[8];  // rows 2k, 2k + 1 (of the lane's 16) of its token
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            pk[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{dz[2 * k], dz[2 * k + 1]}, bf16x2));
+          // rows = tokens: the lane's token row, 4 consecutive vocabulary
+          // values (8 bytes) per 16-byte column q
+          const auto rt = make_rsrc(p.gz_t + ((int64_t)tt * p.kch_v + tile * 8 + wvu * 4 + b) * kPackBlock, kPackBlock);
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{pk[2 * q], pk[2 * q + 1]}, rt, t_off ^ (q << 4),
+                                                  (wtu * TW + 32 * j) * kChunk, 0);
+          // rows = vocabulary: lanes 2m, 2m+1 hold tokens 2m, 2m+1 of rows i,
+          // i+1; after one exchange the even lane stores the token pair of row
+          // i, the odd lane that of row i+1 (4 bytes each)
+          const auto rv = make_rsrc(p.gz_v + ((int64_t)tile * p.kch_t + tt * 8 + wtu * JT + j) * kPackBlock, kPackBlock);
 #pragma unroll
           for (int i = 0; i < 16; i += 2) {
-            const float send = odd ? dz[i] : dz[i + 1];
-            const float recv = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(send), 0xB1, 0xF, 0xF, true));
-            const uint32_t w1 = odd ? pack2(recv, dz[i + 1]) : pack2(dz[i], recv);
-            const int row = wv * 128 + 32 * b + 8 * (i >> 2) + 4 * g + (i & 3) + (odd ? 1 : 0);
-            *reinterpret_cast<uint32_t*>(img + row * kChunk + ((((r32 >> 3) ^ ((row >> 2) & 3))) << 4) +
-                                         2 * (r32 & 6)) = w1;
+            const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)pk[i / 2], 0xB1, 0xF, 0xF, true);
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(pk[i / 2], other, pick), rv,
+                                                  (v_off ^ (i & 4) << 3) + (8 * (i >> 2) + (i & 2)) * kChunk,
+                                                  (wvu * 128 + 32 * b) * kChunk, 0);
           }
         }
       }
-    }
+    };
+    if ((tile + 1) * kTileV > p.V) run(std::true_type{});
+    else run(std::false_type{});
     // The pipeline's waits count outstanding vector-memory operations; these
     // stores would count with the operand loads, so they drain here.
     wait_vmcnt<0>();
@@ -1205,15 +1221,16 @@ __global__ void clear_queue_kernel(int* q) { q[kQueueStride * threadIdx.x] = 0; 
 // Waves per workgroup of each instantiation (measured on the MI355X): two
 // per SIMD where the variant runs faster that way (the per-row FP8 scorer,
 // the measures' passes and the backward's plain products hold their
-// accumulators in VGPRs there); one per SIMD otherwise.  The blockwise
+// accumulators in VGPRs there; the dZ pass of 1531 rows, d = 4096, 1.80 -> 1.71
+// ms, of 10111 rows, d = 2048, 6.35 -> 6.16, of 300 rows 0.68 -> 0.63); one per SIMD otherwise.  The blockwise
 // sampling variants fit their registers at 4 waves (no spills) and run as
 // fast or faster there than at 8 (q8b 85.2 vs 85.4 ms, q17b 27.0 vs
-// 30.6 ms), where they spill around the epilogue; the dZ pass spills at 8.
+// 30.6 ms), where they spill around the epilogue.
 template <int MODE, int EPI>
 constexpr int waves_for() {
   return ((EPI == kEpiSoftmax && (MODE == kBF16 || MODE == kFP8Tensor || MODE == kFP8Row)) ||
           (EPI == kEpiSoftmaxZ && (MODE == kFP8Tensor || MODE == kFP8Row)) ||
-          (EPI == kEpiSoftmaxDiv && MODE == kBF16) || EPI == kEpiStore)
+          (EPI == kEpiSoftmaxDiv && MODE == kBF16) || EPI == kEpiStore || EPI == kEpiGrad)
              ? 8
              : 4;
 }
