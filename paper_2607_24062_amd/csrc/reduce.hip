@@ -388,21 +388,27 @@ __global__ __launch_bounds__(kBatchThreads) void reduce_batch_kernel(acrl_reduce
 // wavefront then takes one group per lane.  Above, a workgroup per group
 // searches for its range instead (64 groups are four turns of 16 wavefronts).
 // 64 responses in 8 groups: 4.1 us (flag, group and batch launches 1.3 + 5.7 +
-// 13.3 us).
+// 13.3 us); 1024 in 64: 13.2 (1.3 + 6.9 + 13.1).
 constexpr int kOneSeqs = 1024, kOneGroups = 64;
 inline bool one_workgroup(int64_t B, int64_t n_groups) { return B <= kOneSeqs && n_groups <= kOneGroups; }
+// Bit k: response lane + 64 k is in group g (-1 past the last response).
+__device__ __forceinline__ uint32_t members(const int32_t* group_of, int g, int lane) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int k = 0; k < kOneSeqs / 64; ++k) m |= (uint32_t)(group_of[lane + 64 * k] == g) << k;
+  return m;
+}
 __global__ __launch_bounds__(1024) void reduce_groups_batch_kernel(acrl_reduce_desc p, const SeqRec* rec) {
   __shared__ int32_t group_of[kOneSeqs];
   __shared__ GroupRec grec[kOneGroups];
   __shared__ BlockShared<8, 64> sh;
   __shared__ BlockShared<1, 64> sh2;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (threadIdx.x < p.B) group_of[threadIdx.x] = p.group_of_seq[threadIdx.x];
+  group_of[threadIdx.x] = threadIdx.x < p.B ? p.group_of_seq[threadIdx.x] : -1;
   __syncthreads();
   for (int g = w; g < p.n_groups; g += 16) {
     GroupSums t;
-    for (int i = lane; i < p.B; i += 64)
-      if (group_of[i] == g) t.add(rec[i]);
+    for (uint32_t m = members(group_of, g, lane); m; m &= m - 1) t.add(rec[lane + 64 * (__ffs(m) - 1)]);
 #pragma unroll
     for (int k = 0; k < 7; ++k) t.v[k] = lane_sum<64>(t.v[k]);
     t.mx = lane_max<64>(t.mx);
@@ -497,7 +503,7 @@ __device__ __forceinline__ void surr_terms(const acrl_surrogate_desc& p, double 
 }
 
 // One workgroup per response (slots as in reduce_seq_kernel: all loaded, no
-// load waits on the mask; 64 responses of 4096 slots 4.6 us, 10.8 one slot at
+// load waits on the mask up to 256 responses; 64 responses of 4096 slots 4.6 us, 10.8 one slot at
 // a time behind its mask with 256 threads).
 template <int NT, bool VEC>
 __global__ __launch_bounds__(NT) void surr_seq_kernel(acrl_surrogate_desc p, SurrSeq* rec) {
@@ -509,6 +515,9 @@ __global__ __launch_bounds__(NT) void surr_seq_kernel(acrl_surrogate_desc p, Sur
     uint8_t m[kSlots];
     float ln[kSlots], lo[kSlots], w[kSlots] = {1.0f, 1.0f, 1.0f, 1.0f}, A[kSlots];
     load_mask<NT, VEC>(p.mask, base, j, p.L, m);
+    // many workgroups a CU hide the wait, and what lies past a response's end is
+    // not read
+    if (p.B > 256 && !(m[0] | m[1] | m[2] | m[3])) continue;
     load_slots<NT, VEC>(p.logp_new, base, j, p.L, ln);
     load_slots<NT, VEC>(p.logp_old, base, j, p.L, lo);
     if (p.weight) load_slots<NT, VEC>(p.weight, base, j, p.L, w);
@@ -573,26 +582,25 @@ __global__ __launch_bounds__(kRedThreads) void surr_batch_kernel(acrl_surrogate_
   surr_loss<kRedThreads>(p, v, sh, prompts);
 }
 
-// Both in one workgroup (see reduce_groups_batch_kernel): 2.3 us, two launches
-// of 2.2 us each otherwise.
+// Both in one workgroup (see reduce_groups_batch_kernel): 64 responses 2.3 us
+// (two launches of 2.2 each otherwise), 1024 in 64 groups 5.9 (3.8 + 2.6).
 __global__ __launch_bounds__(1024) void surr_groups_batch_kernel(acrl_surrogate_desc p, const SurrSeq* rec,
                                                                  double* gG, double* prompts) {
   __shared__ int32_t group_of[kOneSeqs];
   __shared__ double G[kOneGroups], J[kOneGroups];
   __shared__ BlockShared<2, 64> sh;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (threadIdx.x < p.B) group_of[threadIdx.x] = p.group_of_seq[threadIdx.x];
+  group_of[threadIdx.x] = threadIdx.x < p.B ? p.group_of_seq[threadIdx.x] : -1;
   __syncthreads();
   for (int g = w; g < p.n_groups; g += 16) {
     double n = 0, sum = 0;
-    for (int i = lane; i < p.B; i += 64)
-      if (group_of[i] == g) {
-        const SurrSeq r = rec[i];
-        if (r.n > 0) {
-          n += 1.0;
-          sum += r.J / r.n;
-        }
+    for (uint32_t m = members(group_of, g, lane); m; m &= m - 1) {
+      const SurrSeq r = rec[lane + 64 * (__ffs(m) - 1)];
+      if (r.n > 0) {
+        n += 1.0;
+        sum += r.J / r.n;
       }
+    }
     n = lane_sum<64>(n);
     sum = lane_sum<64>(sum);
     if (lane == 0) {
