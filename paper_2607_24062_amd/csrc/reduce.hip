@@ -128,9 +128,9 @@ __device__ __forceinline__ double token_distance(float lp_pi, float lp_mu) {
 }
 
 // Workgroup size of the per-response kernels and the slots of a thread: four
-// per round, consecutive (VEC: 16-byte loads, responses whose slots start
+// per turn, consecutive (VEC: 16-byte loads, responses whose slots start
 // 16-byte aligned) or NT apart.  64 threads take a response of up to 256
-// slots in one round.  Longer ones take 1024 threads while that leaves no
+// slots in one turn.  Longer ones take 1024 threads while that leaves no
 // more than one workgroup per CU, 256 otherwise.
 constexpr int kSlots = 4;
 inline int seq_threads(int64_t B, int64_t L) {
@@ -168,9 +168,9 @@ __device__ __forceinline__ void load_slots(const float* __restrict__ x, int64_t 
 
 // One workgroup per response.  Every slot is loaded (masked ones too: no load
 // waits on the mask).  The sums are plain fp64 sums in slot order; the squared
-// deviations of each round's four slots (about their own mean) merge into the
+// deviations of each turn's four slots (about their own mean) merge into the
 // thread's running Var.  Latency bound: 64 responses of 4096 slots 9.8 us with
-// 256 threads (four rounds of exponentials and divisions), 7.0 with 1024; 4 of
+// 256 threads (four turns of exponentials and divisions), 7.0 with 1024; 4 of
 // 64 slots 5.6 us with 256 threads, 3.4 with 64.
 template <int NT, bool VEC>
 __global__ __launch_bounds__(NT) void reduce_seq_kernel(acrl_reduce_desc p, SeqRec* rec, uint32_t* unsorted) {

@@ -1,6 +1,6 @@
 """GPU parity of the per-response reductions at the edges of their workgroup
 sizes (64 threads up to 256 slots, 256 up to 1024 or more than 256 responses,
-1024 above; four slots a thread and round) and of the one-workgroup group and
+1024 above; four slots a thread at a time) and of the one-workgroup group and
 batch sums (up to 1024 responses in 64 groups), slots 16-byte aligned and not.
 
 Bounds as in the other tests of these entry points: both sides sum the same
