@@ -1451,7 +1451,8 @@ __device__ __forceinline__ void merge_strips(const float* __restrict__ part, int
     const float dM = part[o] - M, ss = part[plane + o], uu = part[2 * plane + o];
     const float a = fast_exp2(dM);
     s1 = fmaf(a, ss, s1);
-    u1 = fmaf(a, fmaf(dM, ss, uu), u1);
+    // (an empty state's U, of logits -inf, may be NaN)
+    u1 = ss == 0.0f ? u1 : fmaf(a, fmaf(dM, ss, uu), u1);
   }
   sh.s[grp][rl] = s1;
   sh.u[grp][rl] = u1;
