@@ -251,8 +251,9 @@ acrl_status acrl_score_pi_mu(const acrl_score_desc* desc, void* stream);
  * seed high 32 bits), as (w >> 9 + 1/2) 2^-23.  The draw is fused into the
  * mu kernel's epilogue: the logits never reach memory, and one generator
  * call serves 32 logits.  logp_mu[r] (nullable) = log mu(a_r).  The draw
- * depends only on (seed, row_offset + r), so chunked calls reproduce one
- * call.
+ * depends only on (seed, row_offset + r), so chunked calls draw the ids of one
+ * call (logp_mu to a few fp32 roundings: its log-sum-exp merges the vocabulary
+ * in parts that the number of rows selects).
  * Requirements: as acrl_score_pi_mu for n_rows, d, V, mu_scaling and the
  * operands; workspace of acrl_score_workspace_size() bytes (with
  * packed_weights, what acrl_score_workspace_query gives for a descriptor with

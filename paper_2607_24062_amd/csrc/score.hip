@@ -717,10 +717,14 @@ void score_kernel(ScoreParams p) {
             // (in increasing order) are one block k = 2 (v0 + 32b) / 32 + g
             // of the draw: its key is the block's log-sum-exp plus one
             // Gumbel, lse2 - log2(-log2 u) in log2 units (a monotone map of
-            // lse - ln(-ln u)), lse2 = M + log2 of the block's share of S
-            // (sh[0], relative to the running maximum M just set).  Only a
-            // block that beats the lane's best so far draws its row: inverse
-            // CDF of the block's softmax with the second uniform.  Uniforms:
+            // lse - ln(-ln u)).  lse2 = M + log2 of the block's share of S
+            // (sh[0], relative to the running maximum M just set) is at hand,
+            // but its rounding depends on M and so on where the strip began:
+            // only a block that comes within that rounding of the lane's best
+            // key, or beats it, forms its key again from its own maximum,
+            // alike in every partition of the vocabulary, and if that one
+            // beats the best so far draws its row: inverse CDF of the block's
+            // softmax with the second uniform.  Uniforms:
             // Philox on counter ((v0 + 32b) / 64, token, g, 0), words 2e and
             // 2e + 1 for e = b mod 2, so one call serves the blocks of b and
             // b + 1 (the second pair is kept in pw).
@@ -738,21 +742,23 @@ void score_kernel(ScoreParams p) {
               wp = pw[j][1];
             }
             const float u = ((float)(wk >> 9) + 0.5f) * 0x1p-23f;
-            const float key = M[j] + __builtin_amdgcn_logf(sh[0]) - __builtin_amdgcn_logf(-__builtin_amdgcn_logf(u));
-            if (key > bk[j]) {
+            const float gum = -__builtin_amdgcn_logf(-__builtin_amdgcn_logf(u));
+            // (the rounding: of exponents up to 2^7, and of M)
+            if (M[j] + __builtin_amdgcn_logf(sh[0]) + gum > bk[j] - fmaf(fabsf(M[j]), 0x1p-20f, 1e-3f)) {
               // the block's row: the first whose cumulative weight exceeds
               // u' times the block's total (in row order), else its last row
-              // of nonzero weight; weights 2^(y - M) as in the sums above
+              // of nonzero weight; weights 2^(y - bm), bm the block's maximum
               const float up = ((float)(wp >> 9) + 0.5f) * 0x1p-23f;
+              auto valid = [&](int i) { return !kTail || (float)(16 * b + i) < nv; };
+              float bm = kInitMax;
+#pragma unroll
+              for (int i = 0; i < 16; ++i) bm = valid(i) ? fmaxf(bm, v[i] * c2[j]) : bm;
               // two passes over the weights (recomputed: fewer live registers)
-              auto weight = [&](int i) {
-                float e = fast_exp2(fmaf(v[i], c2[j], -M[j]));
-                if constexpr (kTail) e *= fminf(fmaxf(nv - (float)(16 * b + i), 0.0f), 1.0f);
-                return e;
-              };
+              auto weight = [&](int i) { return valid(i) ? fast_exp2(fmaf(v[i], c2[j], -bm)) : 0.0f; };
               float tot = 0.0f;
 #pragma unroll
               for (int i = 0; i < 16; ++i) tot += weight(i);
+              const float key = bm + __builtin_amdgcn_logf(tot) + gum;
               const float target = up * tot;
               float c = 0.0f, zsel = 0.0f, zlast = 0.0f;
               int isel = -1, ilast = 0;
@@ -771,9 +777,11 @@ void score_kernel(ScoreParams p) {
                 isel = ilast;
                 zsel = zlast;
               }
-              bk[j] = key;
-              bz[j] = zsel * cz[j];
-              bi[j] = v0 + 32 * b + 8 * (isel >> 2) + 4 * g + (isel & 3);
+              if (key > bk[j]) {
+                bk[j] = key;
+                bz[j] = zsel * cz[j];
+                bi[j] = v0 + 32 * b + 8 * (isel >> 2) + 4 * g + (isel & 3);
+              }
             }
           }
           // the sampled token a_t: rare branch, taken by the one lane holding it
