@@ -130,10 +130,19 @@ __device__ __forceinline__ double token_distance(float lp_pi, float lp_mu) {
 // Workgroup size of the per-response kernels and the slots of a thread: four
 // per turn, consecutive (VEC: 16-byte loads, responses whose slots start
 // 16-byte aligned) or NT apart.  64 threads take a response of up to 256
-// slots in one turn.  Longer ones take 1024 threads while that leaves no
-// more than one workgroup per CU, 256 otherwise.
+// slots in one turn, 256 or 1024 longer ones.  The size decides the order of a
+// response's fp64 sums; the reduce's are outputs, so it goes by L alone there
+// and a chunk of a batch has the sums of the batch.  1024 threads from L = 8193
+// on, GPU time of the call in us, 256 against 1024 threads: 64 responses of
+// 4096 slots 11.1 / 11.0, of 16384 25.2 / 20.5; 1024 responses, where 256
+// threads fill the chip, of 4096 30.1 / 41.7, of 16384 83.9 / 90.3.
 constexpr int kSlots = 4;
-inline int seq_threads(int64_t B, int64_t L) {
+inline int reduce_threads(int64_t L) { return L <= 64 * kSlots ? 64 : L > 8192 ? 1024 : kRedThreads; }
+// The surrogate's sums enter its one loss only: 1024 threads from the second
+// turn on while that leaves no more than one workgroup per CU (64 responses of
+// 4096 slots 9.7 us against 10.6, 256 of 16384 31.5 / 39.8, 1024 of 4096 38.3 /
+// 35.0).
+inline int surr_threads(int64_t B, int64_t L) {
   if (L <= 64 * kSlots) return 64;
   return L > kRedThreads * kSlots && B <= 256 ? 1024 : kRedThreads;
 }
@@ -169,9 +178,8 @@ __device__ __forceinline__ void load_slots(const float* __restrict__ x, int64_t 
 // One workgroup per response.  Every slot is loaded (masked ones too: no load
 // waits on the mask).  The sums are plain fp64 sums in slot order; the squared
 // deviations of each turn's four slots (about their own mean) merge into the
-// thread's running Var.  Latency bound: 64 responses of 4096 slots 9.8 us with
-// 256 threads (four turns of exponentials and divisions), 7.0 with 1024; 4 of
-// 64 slots 5.6 us with 256 threads, 3.4 with 64.
+// thread's running Var.  Latency bound (turns of exponentials and divisions):
+// 4 responses of 64 slots 5.6 us with 256 threads, 3.4 with 64.
 template <int NT, bool VEC>
 __global__ __launch_bounds__(NT) void reduce_seq_kernel(acrl_reduce_desc p, SeqRec* rec, uint32_t* unsorted) {
   __shared__ BlockShared<5, NT> sh;
@@ -650,14 +658,14 @@ __global__ __launch_bounds__(256) void surr_coef_kernel(acrl_surrogate_desc p, c
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline bool aligned(const void* q, uintptr_t a) { return ((uintptr_t)q & (a - 1)) == 0; }
 
-// launch(workgroup size, 16-byte slots) of a per-response kernel.
+// launch(workgroup size, 16-byte slots) of a per-response kernel of nt threads.
 template <typename F>
-inline void launch_seq(int64_t B, int64_t L, bool vec, F&& launch) {
-  auto with = [&](auto nt) {
-    if (vec) launch(nt, std::true_type{});
-    else launch(nt, std::false_type{});
+inline void launch_seq(int nt, bool vec, F&& launch) {
+  auto with = [&](auto n) {
+    if (vec) launch(n, std::true_type{});
+    else launch(n, std::false_type{});
   };
-  switch (seq_threads(B, L)) {
+  switch (nt) {
     case 64: return with(std::integral_constant<int, 64>{});
     case 1024: return with(std::integral_constant<int, 1024>{});
     default: return with(std::integral_constant<int, kRedThreads>{});
@@ -682,7 +690,7 @@ hipError_t launch_surrogate(const acrl_surrogate_desc& p, hipStream_t s) {
   if (p.B > 0) {
     const bool vec = p.L % kSlots == 0 && aligned(p.logp_new, 16) && aligned(p.logp_old, 16) && aligned(p.mask, 4) &&
                      aligned(p.weight, 16) && (!p.adv_per_token || aligned(p.adv, 16));
-    launch_seq(p.B, p.L, vec, [&](auto nt, auto v) {
+    launch_seq(surr_threads(p.B, p.L), vec, [&](auto nt, auto v) {
       constexpr int NT = decltype(nt)::value;
       hipLaunchKernelGGL((surr_seq_kernel<NT, decltype(v)::value>), dim3((unsigned)p.B), dim3(NT), 0, s, p, rec);
     });
@@ -726,7 +734,7 @@ hipError_t launch_reduce(const acrl_reduce_desc& p, hipStream_t s) {
     // 16-byte slot loads when every row of slots starts 16-byte aligned
     const bool vec = p.L % kSlots == 0 && aligned(p.logp_pi, 16) && aligned(p.logp_mu, 16) && aligned(p.mask, 4) &&
                      aligned(p.entropy_pi, 16) && aligned(p.entropy_mu, 16) && aligned(p.d_tok, 16);
-    launch_seq(p.B, p.L, vec, [&](auto nt, auto v) {
+    launch_seq(reduce_threads(p.L), vec, [&](auto nt, auto v) {
       constexpr int NT = decltype(nt)::value;
       hipLaunchKernelGGL((reduce_seq_kernel<NT, decltype(v)::value>), dim3((unsigned)p.B), dim3(NT), 0, s, p, rec,
                          one ? nullptr : unsorted);

@@ -1,6 +1,7 @@
 """GPU parity of the per-response reductions at the edges of their workgroup
-sizes (64 threads up to 256 slots, 256 up to 1024 or more than 256 responses,
-1024 above; four slots a thread at a time) and of the one-workgroup group and
+sizes (reduce: 64 threads up to 256 slots, 256 up to 8192, 1024 above;
+surrogate: 256 up to 1024 slots or of more than 256 responses, 1024 above; four
+slots a thread at a time) and of the one-workgroup group and
 batch sums (up to 1024 responses in 64 groups), slots 16-byte aligned and not.
 
 Bounds as in the other tests of these entry points: both sides sum the same
@@ -15,7 +16,8 @@ from gpu_util import down, torch_dev, up
 pytestmark = pytest.mark.gpu
 
 # (B, L, groups)
-SHAPES = [(3, 256, 2), (3, 257, 2), (2, 1023, 2), (2, 1024, 1), (3, 1025, 2), (2, 4096, 2), (2, 4097, 1), (1, 9000, 1),
+SHAPES = [(3, 256, 2), (3, 257, 2), (2, 1023, 2), (2, 1024, 1), (3, 1025, 2), (2, 4096, 2), (2, 4097, 1), (2, 8192, 1),
+          (2, 8193, 1), (1, 9000, 1),
           (256, 1028, 32), (257, 1028, 32), (1023, 7, 63), (1024, 8, 64), (1024, 8, 65), (1025, 8, 64), (70, 8, 64)]
 
 
