@@ -317,6 +317,9 @@ acrl_status acrl_pack_weights(const void* w, const void* wq, const void* wq_scal
  * with another id belongs to no group and enters no batch statistic).
  * Grouping the responses of a prompt together (non-decreasing group_of_seq)
  * lets each group find its responses by binary search instead of a scan.
+ * A response's results do not depend on the other responses of the call, nor
+ * (grouped so, and of up to 64 responses) a group's on the other groups: a
+ * chunk of a batch gives the batch's bits.
  */
 typedef struct acrl_reduce_desc {
   int64_t B;                    /* responses                                                */

@@ -69,6 +69,12 @@ __device__ __forceinline__ double lane_max(double v) {
   return v;
 }
 
+__device__ __forceinline__ double first_lane(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
 // Sums of NS values and the maximum of mx over a workgroup of NT = 64, 256 or
 // 1024 threads, one barrier (none for a wavefront): trees inside each
 // wavefront, then every thread's lane group of NT / 64 lanes takes one
@@ -281,6 +287,7 @@ struct GroupSums {
       var = var_merge(var, Var{r.n, mean, r.m2});
     }
   }
+  __device__ __forceinline__ double mean_d() const { return v[2] > 0 ? v[3] / v[2] : 0.0; }
 };
 
 // Group g's outputs and record from its sums (mu, m2: its tokens' mean d and
@@ -334,7 +341,7 @@ __global__ __launch_bounds__(kRedThreads) void reduce_group_kernel(acrl_reduce_d
   for (int64_t i = lo + threadIdx.x; i < hi; i += kRedThreads)
     if (sorted || p.group_of_seq[i] == g) t.add(rec[i]);
   block_stats<7, kRedThreads>(t.v, t.mx, sh);
-  const double mu = t.v[2] > 0 ? t.v[3] / t.v[2] : 0.0;
+  const double mu = t.mean_d();
   double m2[1] = {var_about(t.var, mu)}, unused = 0.0;
   block_stats<1, kRedThreads>(m2, unused, sh2);
   if (threadIdx.x == 0) grec[g] = store_group(p, g, t, mu, m2[0]);
@@ -391,12 +398,16 @@ __global__ __launch_bounds__(kBatchThreads) void reduce_batch_kernel(acrl_reduce
 }
 
 // The groups and the batch in one workgroup, for up to kOneSeqs responses in
-// up to kOneGroups groups: a wavefront takes a group at a time and looks
-// through the responses' groups in LDS, in whatever order they come; the first
-// wavefront then takes one group per lane.  Above, a workgroup per group
-// searches for its range instead (64 groups are four turns of 16 wavefronts).
-// 64 responses in 8 groups: 4.1 us (flag, group and batch launches 1.3 + 5.7 +
-// 13.3 us); 1024 in 64: 13.2 (1.3 + 6.9 + 13.1).
+// up to kOneGroups groups: a wavefront takes a group at a time, its range where
+// group_of_seq is non-decreasing, else what it finds in the responses' groups
+// in LDS; the first wavefront then takes one group per lane.  Above, a
+// workgroup per group searches for its range instead.  Where group_of_seq is
+// non-decreasing lane k of either takes the group's k-th response, so a group
+// of up to 64 has the same sums wherever it stands and whatever else is in the
+// batch.  GPU time of the whole call, this against a workgroup per group, us:
+// 64 responses in 8 groups 8.0 / 15.0, 1024 in 32 11.5 / 15.9, 1024 in 64 16.8 /
+// 16.0 (the surrogate's 8.0 / 9.6, 9.8 / 10.9, 11.8 / 11.0); with 64 groups the
+// launches less still save the host 4 us of 26 (of 21).
 constexpr int kOneSeqs = 1024, kOneGroups = 64;
 inline bool one_workgroup(int64_t B, int64_t n_groups) { return B <= kOneSeqs && n_groups <= kOneGroups; }
 // Bit k: response lane + 64 k is in group g (-1 past the last response).
@@ -408,21 +419,40 @@ __device__ __forceinline__ uint32_t members(const int32_t* group_of, int g, int 
 }
 __global__ __launch_bounds__(1024) void reduce_groups_batch_kernel(acrl_reduce_desc p, const SeqRec* rec) {
   __shared__ int32_t group_of[kOneSeqs];
+  __shared__ int lo[kOneGroups], hi[kOneGroups], disorder[16];
   __shared__ GroupRec grec[kOneGroups];
   __shared__ BlockShared<8, 64> sh;
   __shared__ BlockShared<1, 64> sh2;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  group_of[threadIdx.x] = threadIdx.x < p.B ? p.group_of_seq[threadIdx.x] : -1;
+  // the groups' ranges lo .. hi - 1 where they are in order, noted by the
+  // responses at their ends (those of a group without responses stay unwritten)
+  const int i = threadIdx.x, ng = (int)p.n_groups, n = (int)p.B;
+  const int mine = i < n ? p.group_of_seq[i] : -1;
+  const int before = i > 0 && i < n ? p.group_of_seq[i - 1] : -1;
+  const int after = i + 1 < n ? p.group_of_seq[i + 1] : -1;
+  group_of[i] = mine;
+  if (mine >= 0 && mine < ng) {
+    if (mine != before) lo[mine] = i;
+    if (mine != after) hi[mine] = i + 1;
+  }
+  const bool wrong = __any(i > 0 && i < n && mine < before);
+  if (lane == 0) disorder[w] = wrong;
   __syncthreads();
+  const bool sorted = !__any(disorder[lane & 15] != 0);
   for (int g = w; g < p.n_groups; g += 16) {
     GroupSums t;
-    for (uint32_t m = members(group_of, g, lane); m; m &= m - 1) t.add(rec[lane + 64 * (__ffs(m) - 1)]);
+    if (sorted) {
+      const int first = lo[g] & (kOneSeqs - 1);  // (any value if the group has no response)
+      const int last = group_of[first] == g ? hi[g] : 0;
+      for (int k = first + lane; k < last; k += 64) t.add(rec[k]);
+    } else {
+      for (uint32_t m = members(group_of, g, lane); m; m &= m - 1) t.add(rec[lane + 64 * (__ffs(m) - 1)]);
+    }
 #pragma unroll
     for (int k = 0; k < 7; ++k) t.v[k] = lane_sum<64>(t.v[k]);
     t.mx = lane_max<64>(t.mx);
-    const double mu = t.v[2] > 0 ? t.v[3] / t.v[2] : 0.0;
-    const double m2 = lane_sum<64>(var_about(t.var, mu));
-    if (lane == 0) grec[g] = store_group(p, g, t, mu, m2);
+    const double m2 = lane_sum<64>(var_about(t.var, first_lane(t.mean_d())));
+    if (lane == 0) grec[g] = store_group(p, g, t, t.mean_d(), m2);
   }
   __syncthreads();
   if (w != 0) return;
