@@ -1268,11 +1268,16 @@ inline int device_cus() {
 template <int MODE, int EPI, int NW, int JT>
 void launch_tile(unsigned grid, const ScoreParams& p, hipStream_t s) {
   constexpr bool kPersist = !(MODE == kFP8Row && EPI == kEpiSoftmaxZ);
-  // the measures' passes spill more with the row-major addressing in them (92
-  // instead of 40 bytes per lane; 2900 rows, d = 2048: 3.14 against 3.03 ms),
-  // so they have a copy for each; the products' operands are always packed;
-  // the others run packed images as fast either way
-  constexpr bool kOwnCopy = EPI == kEpiSoftmaxZ || EPI == kEpiSoftmaxDiv;
+  // The row-major addressing costs registers, so where they are short packed
+  // operands take an instantiation without it: the 8-wave 256-token scorers
+  // spill 24 bytes a lane (per-tensor) and 12 (per-row) instead of 44 and 28, the
+  // measures' passes 40 and 12 instead of 92 and 28.  pi of 20480 and 40960 rows,
+  // d = 4096: 20.1 and 39.6 ms with it apart, 20.3 and 40.3 in one; measures of
+  // 2900 rows, d = 2048, 3.03 and 3.14.  The 4-wave kernels and dZ do not spill
+  // either way: the draws and the 64-token tiles run packed images within 1 % of
+  // a copy of their own, MXFP8 scoring 2 % faster than that (5003 rows, d = 4096:
+  // 2.67 against 2.79 ms).  The products' operands are always packed.
+  constexpr bool kOwnCopy = (EPI == kEpiSoftmax && NW == 8) || EPI == kEpiSoftmaxZ || EPI == kEpiSoftmaxDiv;
   auto launch = [&](auto rowmajor_tag) {
     constexpr bool kRowMajor = decltype(rowmajor_tag)::value;
     if constexpr (kPersist) {
