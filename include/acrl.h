@@ -155,7 +155,8 @@ acrl_status acrl_fp8_encode(const float* x, int64_t n, int rounding, void* q, vo
  * token ids in [0, V) (else the row's outputs are NaN and *error_flag, if
  * given, becomes nonzero; the flag is never cleared by the library).
  * The workspace holds a tiled copy of h and hq and of the E8M0 scales of Wq and
- * hq, for calls of many rows (above 12288) also of W and Wq (then about
+ * hq, for calls of many rows also of W and Wq (both above 12288 rows, 8192 with
+ * the measures below, an MXFP8 Wq above 3072; then about
  * (3 + 1/32) (V + n_rows) d bytes; with fewer rows W and Wq are read where
  * they lie), besides the per-strip partial states and the work-queue counters
  * of the persistent launches (cleared by the call itself); with
@@ -480,11 +481,11 @@ acrl_status acrl_surrogate(const acrl_surrogate_desc* desc, void* stream);
  * Requirements: n_rows >= 0; d > 0, d % 128 == 0; 0 < V < 2^23;
  * (V rounded up to 256) * d / 8 < 2^32; token_chunk >= 0 (0 = 16384; rounded
  * up to a multiple of 256; at most 2^23); workspace of
- * acrl_backward_workspace_size() bytes (packed W above 4096 rows, W^T, one chunk of H, H^T
- * and two bf16 copies of its dZ: about 4 V d + 4 c d + 4 c V bytes for a
- * chunk of c rows; plus at most 512 MiB of fp32 partial products where a
- * product of few output tiles is split along K, and the products' work-queue
- * counters, cleared by the call).                                           */
+ * acrl_backward_workspace_size() bytes (W^T, packed W above min(4 d, 16384)
+ * rows, one chunk of H, H^T and two bf16 copies of its dZ: about
+ * 4 V d + 4 c d + 4 c V bytes for a chunk of c rows; plus at most 512 MiB of
+ * fp32 partial products where a product of few output tiles is split along K,
+ * and the products' work-queue counters, cleared by the call).              */
 typedef struct acrl_backward_desc {
   int64_t n_rows;
   int64_t d;

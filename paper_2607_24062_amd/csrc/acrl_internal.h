@@ -37,7 +37,7 @@ struct ScorePlan {
   int tiles_per_strip;  // vocabulary tiles per workgroup
   int n_strips;         // vocabulary strips (partial softmax states per row)
   Raster raster;
-  bool pack_w;          // W and Wq are packed by the call (else prepacked, or read in place)
+  bool pack_w, pack_wq; // W / Wq are packed by the call (else prepacked, or read in place)
   size_t ws_part_offset[2];  // byte offsets of the (M, S, U) partials of pi / mu
   size_t ws_logit_offset[2]; // byte offsets of the sampled-token logits of pi / mu
   size_t ws_pack_offset[4];  // byte offsets of the packed W, H (bf16) and Wq, Hq (e4m3)
@@ -50,10 +50,10 @@ struct ScorePlan {
   size_t ws_queue_offset;    // the persistent grid's per-XCD claim counters
   size_t ws_bytes;
 };
-// div_rows > 0 plans the full-vocabulary measures in passes of div_rows rows;
+// mx: mu is MXFP8; div_rows > 0 plans the full-vocabulary measures in passes of div_rows rows;
 // prepacked: W's and Wq's images come from the caller;
 // narrow: token tiles of 64 and 128 rows may be planned (scoring, sampling).
-ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows, bool prepacked, bool narrow);
+ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, bool mx, int64_t div_rows, bool prepacked, bool narrow);
 constexpr int64_t kDivergenceChunk = 16384;  // default rows per pass of the full-vocabulary measures
 // Caller-owned packed LM head (acrl_pack_weights): byte offsets of the W,
 // Wq and Wq-MX-scale images.

@@ -237,7 +237,7 @@ acrl_status acrl_score_workspace_size(int64_t n_rows, int64_t d, int64_t V, int 
   ACRL_REQUIRE(V > 0 && V < (int64_t)INT32_MAX - 512, "V out of range");
   ACRL_REQUIRE(mu_scaling >= ACRL_SCALE_PER_TENSOR && mu_scaling <= ACRL_SCALE_MX32, "mu_scaling unknown");
   ACRL_REQUIRE(acrl::score_size_ok(V, d) && acrl::score_size_ok(n_rows, d), "rows x d too large");
-  *bytes = acrl::plan_score(n_rows, d, V, 0, false, true).ws_bytes;
+  *bytes = acrl::plan_score(n_rows, d, V, mu_scaling == ACRL_SCALE_MX32, 0, false, true).ws_bytes;
   return ACRL_OK;
 }
 
@@ -246,7 +246,9 @@ acrl_status acrl_score_div_workspace_size(int64_t n_rows, int64_t d, int64_t V, 
   acrl_status st = acrl_score_workspace_size(n_rows, d, V, mu_scaling, bytes);
   if (st != ACRL_OK) return st;
   ACRL_REQUIRE(div_chunk >= 0 && div_chunk <= ((int64_t)1 << 24), "div_chunk must lie in [0, 2^24]");
-  *bytes = acrl::plan_score(n_rows, d, V, div_chunk > 0 ? div_chunk : acrl::kDivergenceChunk, false, true).ws_bytes;
+  *bytes = acrl::plan_score(n_rows, d, V, mu_scaling == ACRL_SCALE_MX32,
+                            div_chunk > 0 ? div_chunk : acrl::kDivergenceChunk, false, true)
+               .ws_bytes;
   return ACRL_OK;
 }
 
@@ -255,8 +257,8 @@ acrl_status acrl_score_workspace_query(const acrl_score_desc* desc, size_t* byte
   acrl_status st = acrl_score_workspace_size(desc->n_rows, desc->d, desc->V, desc->mu_scaling, bytes);
   if (st != ACRL_OK) return st;
   ACRL_REQUIRE(desc->div_chunk >= 0 && desc->div_chunk <= ((int64_t)1 << 24), "div_chunk must lie in [0, 2^24]");
-  *bytes = acrl::plan_score(desc->n_rows, desc->d, desc->V, acrl::div_rows_of(desc), desc->packed_weights != nullptr,
-                             true)
+  *bytes = acrl::plan_score(desc->n_rows, desc->d, desc->V, desc->mu_scaling == ACRL_SCALE_MX32,
+                            acrl::div_rows_of(desc), desc->packed_weights != nullptr, true)
                .ws_bytes;
   return ACRL_OK;
 }
@@ -293,7 +295,8 @@ acrl_status acrl_score_pi_mu(const acrl_score_desc* desc, void* stream) {
   acrl_status st = acrl::validate_score(desc);
   if (st != ACRL_OK) return st;
   ACRL_REQUIRE(desc->div_chunk >= 0 && desc->div_chunk <= ((int64_t)1 << 24), "div_chunk must lie in [0, 2^24]");
-  const acrl::ScorePlan plan = acrl::plan_score(desc->n_rows, desc->d, desc->V, acrl::div_rows_of(desc),
+  const acrl::ScorePlan plan = acrl::plan_score(desc->n_rows, desc->d, desc->V, desc->mu_scaling == ACRL_SCALE_MX32,
+                                                acrl::div_rows_of(desc),
                                                 desc->packed_weights != nullptr, true);
   if (desc->n_rows > 0 && (!desc->workspace || desc->workspace_bytes < plan.ws_bytes)) {
     set_error("acrl_score_pi_mu needs %zu workspace bytes, got %zu", plan.ws_bytes, desc->workspace_bytes);
@@ -334,7 +337,8 @@ acrl_status acrl_sample_mu(const acrl_sample_desc* d, void* stream) {
     ACRL_REQUIRE(d->hq && d->hq_scales && d->ids, "hq, hq_scales and ids are required");
     ACRL_REQUIRE(acrl::aligned16(d->hq) && acrl::aligned16(d->hq_scales), "hq and hq_scales must be 16-byte aligned");
   }
-  const acrl::ScorePlan plan = acrl::plan_score(d->n_rows, d->d, d->V, 0, d->packed_weights != nullptr, true);
+  const acrl::ScorePlan plan = acrl::plan_score(d->n_rows, d->d, d->V, d->mu_scaling == ACRL_SCALE_MX32, 0,
+                                                d->packed_weights != nullptr, true);
   if (d->n_rows > 0 && (!d->workspace || d->workspace_bytes < plan.ws_bytes)) {
     set_error("acrl_sample_mu needs %zu workspace bytes, got %zu", plan.ws_bytes, d->workspace_bytes);
     return ACRL_ERR_WORKSPACE;

@@ -1732,14 +1732,23 @@ Raster raster_blocks(int n_ttiles, int n_strips) {
 // Calls of at most this many rows read a W that the caller did not pack where
 // it lies, row-major: a 1 KiB load then takes half a 128-byte line of 16 rows
 // and the other half comes from L2 with the next chunk, which costs the
-// kernels 2-4 % (16384 rows, d = 4096: pi 16.95 against 16.45 ms, mu 8.15
-// against 8.0), while the packed copy costs three passes over W (0.49 and
-// 0.24 ms): 1017 rows, d = 4096, pi 2.01 -> 1.13 ms, mu 1.04 -> 0.56; 64 rows
-// 0.72 -> 0.25 and 0.37 -> 0.14 ms; even at about 15000 rows.  The backward's
-// 4-wave dZ pass loses ~8 %, so its line is lower: 1017 rows, d = 4096,
-// 5.03 -> 4.55 ms; 4096 rows, d = 2048, 7.44 -> 7.31 ms; 10111 rows 16.9 ->
-// 17.2 ms.  (The row offset is a 24-bit product.)
-constexpr int64_t kReadInPlaceRows = 12288, kBackwardInPlaceRows = 4096;
+// kernels 1-4 %, while the packed copy costs three passes over W.  Packed by
+// the call against read in place, ms, V = 151936:
+//  - pi, d = 4096: 2048 rows 2.57 / 2.16, 8192 8.73 / 8.45, 12288 12.9 / 12.7,
+//    16384 16.8 / 16.8; mu 2.25 / 2.07 at 4096, 6.30 / 6.20 at 12288, 8.14 / 8.20
+//    at 16384; draws (4 waves) 2.45 / 2.34 at 4096, even from 8192 on;
+//  - the measures (their passes spill more in place), d = 2048: 4096 rows
+//    4.31 / 4.10, 8192 8.03 / 7.98, 12288 11.93 / 12.01;
+//  - MXFP8, d = 4096: mu 1.33 / 1.19 at 2048 rows, 2.35 / 2.33 at 4096, draws 1.42 /
+//    1.30 and 2.53 / 2.55, 4.79 / 4.97 at 8192; d = 2048: draws 0.82 / 0.78, 1.49 /
+//    1.53 and 2.78 / 3.00;
+//  - the backward, whose copy is W's alone and whose line rises with d (up to
+//    4 d rows, 16384 at most): d = 4096 4.55 / 4.10 at 1024 rows, 39.6 / 38.9 at
+//    12288, 53.1 / 51.8 at 16384; d = 2048 7.16 / 7.08 at 4096, 13.42 / 13.40 at 8192,
+//    26.5 / 26.6 at 16384; d = 1024, V = 30000 0.827 / 0.804 at 4096, 0.987 / 0.994 at
+//    5000, 2.25 / 2.28 at 12000.
+// (The row offset is a 24-bit product.)
+constexpr int64_t kReadInPlaceRows = 12288, kMeasuresInPlaceRows = 8192, kMxInPlaceRows = 3072;
 static bool read_in_place(int64_t n_rows, int64_t d, int64_t most) {
   return n_rows <= most && 2 * d < ((int64_t)1 << 24);
 }
@@ -1758,7 +1767,7 @@ static void set_raster(ScoreParams& p, const Raster& r) {
   p.n_blocks = r.n_blocks;
 }
 
-ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows, bool prepacked, bool narrow) {
+ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, bool mx, int64_t div_rows, bool prepacked, bool narrow) {
   ScorePlan pl{};
   pl.n_ptiles = (int)((n_rows + kTileT - 1) / kTileT);
   pl.n_vtiles = (int)((V + kTileV - 1) / kTileV);
@@ -1831,12 +1840,14 @@ ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, int64_t div_rows, boo
   // packed operands: W, H (2d bytes per row), Wq, Hq (d bytes per row); the
   // weight images only when they do not come prepacked by the caller and the
   // rows are too many to read W and Wq in place
-  pl.pack_w = !prepacked && !read_in_place(n_rows, d, kReadInPlaceRows);
+  const int64_t in_place = div_rows > 0 ? kMeasuresInPlaceRows : kReadInPlaceRows;
+  pl.pack_w = !prepacked && !read_in_place(n_rows, d, in_place);
+  pl.pack_wq = !prepacked && !read_in_place(n_rows, d, mx ? kMxInPlaceRows : in_place);
   const size_t vrows = (size_t)pl.n_vtiles * kTileV, trows = (size_t)pl.n_ptiles * kTileT;
   const size_t pack_bytes[4] = {vrows * 2 * (size_t)d, trows * 2 * (size_t)d, vrows * (size_t)d, trows * (size_t)d};
   for (int q = 0; q < 4; ++q) {
     pl.ws_pack_offset[q] = off;
-    if (pl.pack_w || q == 1 || q == 3) off += align_up(pack_bytes[q], 256);
+    if (q == 0 ? pl.pack_w : q == 2 ? pl.pack_wq : true) off += align_up(pack_bytes[q], 256);
   }
   // MX: packed E8M0 scale images of Wq and Hq (d/32 bytes per row)
   const size_t mx_bytes[2] = {vrows * (size_t)(d / 32), trows * (size_t)(d / 32)};
@@ -1899,7 +1910,7 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
   const int64_t src_tiles[4] = {pl.n_vtiles, pl.n_ptiles, pl.n_vtiles, pl.n_ptiles};
   for (int q = 0; q < 4; ++q) {
     if (!(q < 2 ? do_pi : do_mu)) continue;
-    if (!pl.pack_w && (q == 0 || q == 2)) continue;
+    if ((q == 0 && !pl.pack_w) || (q == 2 && !pl.pack_wq)) continue;
     const int64_t row_bytes = q < 2 ? 2 * dsc.d : dsc.d;
     const int64_t units = src_tiles[q] * kTileV * (row_bytes / 16);
     const unsigned blocks = (unsigned)std::min<int64_t>((units + 255) / 256, 8192);
@@ -1911,7 +1922,7 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
   pp.b = ws + pl.ws_pack_offset[1];
   pp.n_chunks = (int)(2 * dsc.d / kChunk);
   const void* w_at = pw ? pw + pwl.w_offset : pl.pack_w ? ws + pl.ws_pack_offset[0] : dsc.w;
-  const void* wq_at = pw ? pw + pwl.wq_offset : pl.pack_w ? ws + pl.ws_pack_offset[2] : dsc.wq;
+  const void* wq_at = pw ? pw + pwl.wq_offset : pl.pack_wq ? ws + pl.ws_pack_offset[2] : dsc.wq;
   set_a(pp, w_at, pw || pl.pack_w);
   pp.part = reinterpret_cast<float*>(ws + pl.ws_part_offset[0]);
   pp.logit = reinterpret_cast<float*>(ws + pl.ws_logit_offset[0]);
@@ -1920,7 +1931,7 @@ hipError_t launch_score(const acrl_score_desc& dsc, const ScorePlan& pl, hipStre
   ScoreParams pm = pp;
   pm.b = ws + pl.ws_pack_offset[3];
   pm.n_chunks = (int)(dsc.d / kChunk);
-  set_a(pm, wq_at, pw || pl.pack_w);
+  set_a(pm, wq_at, pw || pl.pack_wq);
   pm.part = reinterpret_cast<float*>(ws + pl.ws_part_offset[1]);
   pm.logit = reinterpret_cast<float*>(ws + pl.ws_logit_offset[1]);
   if (dsc.mu_scaling == ACRL_SCALE_MX32) {
@@ -2098,7 +2109,7 @@ BackwardPlan plan_backward(int64_t n_rows, int64_t d, int64_t V, int64_t chunk) 
     off += align_up(bytes, 256);
     return o;
   };
-  pl.pack_w = !read_in_place(n_rows, d, kBackwardInPlaceRows);
+  pl.pack_w = !read_in_place(n_rows, d, std::min<int64_t>(4 * d, 16384));
   pl.off_w = take(pl.pack_w ? vrows * 2 * (size_t)d : 0);  // W, rows = vocabulary, K = d (many rows: else read in place)
   pl.off_wt = take(drows * vrows * 2);                     // W^T, rows = d, K = vocabulary
   pl.off_h = take(crows * 2 * (size_t)d);                  // H chunk, rows = tokens, K = d
@@ -2189,7 +2200,7 @@ hipError_t launch_backward(const acrl_backward_desc& dsc, const BackwardPlan& pl
                          rows, d, pl.n_dtiles, kch_t, img_ht);
     // dZ of the chunk from the recomputed logits (vocabulary strips as in scoring)
     {
-      const ScorePlan sp = plan_score(rows, d, V, 0, true, false);
+      const ScorePlan sp = plan_score(rows, d, V, false, 0, true, false);
       ScoreParams pg{};
       pg.b = img_h;
       pg.n_chunks = (int)(2 * d / kChunk);
@@ -2235,7 +2246,7 @@ hipError_t launch_sample(const acrl_sample_desc& dsc, const ScorePlan& pl, hipSt
   const int64_t src_rows[2] = {dsc.V, dsc.n_rows};
   const int64_t src_tiles[2] = {pl.n_vtiles, pl.n_ptiles};
   for (int q = 0; q < 2; ++q) {
-    if (q == 0 && !pl.pack_w) continue;
+    if (q == 0 && !pl.pack_wq) continue;
     const int64_t units = src_tiles[q] * kTileV * (dsc.d / 16);
     const unsigned blocks = (unsigned)std::min<int64_t>((units + 255) / 256, 8192);
     hipLaunchKernelGGL(pack_kernel, dim3(blocks), dim3(256), 0, s, static_cast<const uint8_t*>(srcs[q]),
@@ -2254,8 +2265,8 @@ hipError_t launch_sample(const acrl_sample_desc& dsc, const ScorePlan& pl, hipSt
   pm.queue = reinterpret_cast<int*>(ws + pl.ws_queue_offset);
   pm.b = ws + pl.ws_pack_offset[3];
   pm.n_chunks = (int)(dsc.d / kChunk);
-  const void* wq_at = pw ? pw + pwl.wq_offset : pl.pack_w ? ws + pl.ws_pack_offset[2] : dsc.wq;
-  set_a(pm, wq_at, pw || pl.pack_w);
+  const void* wq_at = pw ? pw + pwl.wq_offset : pl.pack_wq ? ws + pl.ws_pack_offset[2] : dsc.wq;
+  set_a(pm, wq_at, pw || pl.pack_wq);
   pm.part = reinterpret_cast<float*>(ws + pl.ws_part_offset[1]);
   pm.seed_lo = (uint32_t)dsc.seed;
   pm.seed_hi = (uint32_t)(dsc.seed >> 32);

@@ -75,10 +75,12 @@ def test_workspace_grows_with_rows():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("scaling", [oracle.PER_TENSOR, oracle.PER_ROW, oracle.MX32])
-@pytest.mark.parametrize("T,V", [(1, 100), (130, 300), (700, 1000), (12288, 300), (12289, 300)])
+@pytest.mark.parametrize("T,V", [(1, 100), (130, 300), (700, 1000), (3072, 300), (3073, 300), (8192, 300), (8193, 300),
+                                 (12288, 300), (12289, 300)])
 def test_weights_read_in_place_equal_packed(scaling, T, V):
-    """W and Wq read where they lie (up to 12288 rows), packed by the call
-    (above) and packed by the caller: the same bits everywhere."""
+    """W and Wq read where they lie (up to 12288 rows, 8192 with the measures, an
+    MXFP8 Wq up to 3072), packed by the call (above) and packed by the caller:
+    the same bits everywhere."""
     torch, dev = torch_dev()
     from paper_2607_24062_amd import acrl
     h, w = up_bf16(torch, dev, random_bf16((T, 256), 31)), up_bf16(torch, dev, random_bf16((V, 256), 32, std=0.2))
@@ -101,13 +103,40 @@ def test_weights_read_in_place_equal_packed(scaling, T, V):
 def test_backward_weights_read_in_place_equal_packed():
     torch, dev = torch_dev()
     from paper_2607_24062_amd import acrl
-    T, V, d = 4097, 1000, 256
+    T, V, d = 4 * 256 + 1, 1000, 256
     h, w = up_bf16(torch, dev, random_bf16((T, d), 41)), up_bf16(torch, dev, random_bf16((V, d), 42, std=0.2))
     r = np.random.default_rng(43)
     ids = up(torch, dev, r.integers(0, V, size=T).astype(np.int32))
     coef = up(torch, dev, r.normal(0, 1e-2, size=T).astype(np.float32))
     lse = up(torch, dev, np.full(T, 8.0, np.float32))  # any lse: the same recomputed probabilities on both paths
-    a, _ = acrl.acrl_lm_head_backward(h, w, ids, coef, lse, want_dw=False)          # packs W
-    b, _ = acrl.acrl_lm_head_backward(h[:-1], w, ids[:-1], coef[:-1], lse[:-1], want_dw=False)  # reads it in place
+    coef[-1] = 0
+    a, aw = acrl.acrl_lm_head_backward(h, w, ids, coef, lse)                          # packs W
+    b, bw = acrl.acrl_lm_head_backward(h[:-1], w, ids[:-1], coef[:-1], lse[:-1])  # reads it in place
     torch.cuda.synchronize()
     assert np.array_equal(down(a)[:-1], down(b))
+    # one K chunk more moves the slices of dW's sum: fp32 sums of 1024 terms, 2^-24 each, in another order
+    assert float((aw - bw).norm() / aw.norm()) <= 1e-5
+
+
+def test_workspace_holds_the_packed_weights_above_the_lines():
+    """An unpacked call's workspace has room for a packed W above 12288 rows, 8192 with the measures, and for a
+    packed Wq likewise, of MXFP8 above 3072 (host arithmetic only)."""
+    from paper_2607_24062_amd import acrl
+    L = acrl.lib()
+    V, d = 151936, 2048
+    buf = ctypes.c_void_p(256)
+
+    def extra(n, scaling, div):  # bytes beyond the call's that brings packed weights, in images of Wq (2 of W)
+        nb = []
+        for pw in (None, buf):
+            desc = acrl.ScoreDesc(n_rows=n, d=d, V=V, mu_scaling=scaling, packed_weights=pw, l2=buf if div else None)
+            v = ctypes.c_size_t()
+            assert L.acrl_score_workspace_query(ctypes.byref(desc), ctypes.byref(v)) == 0
+            nb.append(v.value)
+        return (nb[0] - nb[1]) // (V * d)
+
+    for scaling in (acrl.SCALE_PER_TENSOR, acrl.SCALE_PER_ROW):
+        assert [extra(n, scaling, False) for n in (1, 4096, 12288, 12289)] == [0, 0, 0, 3]
+        assert [extra(n, scaling, True) for n in (1, 8192, 8193)] == [0, 0, 3]
+    assert [extra(n, acrl.SCALE_MX32, False) for n in (1, 3072, 3073, 12288, 12289)] == [0, 0, 1, 1, 3]
+    assert [extra(n, acrl.SCALE_MX32, True) for n in (1, 3072, 3073, 8192, 8193)] == [0, 0, 1, 1, 3]
