@@ -184,13 +184,29 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+# the current stream's handle alone, where torch has it: making its Stream
+# object takes 2.7 us, twice per call, and the handle 0.1
+_current_raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_zero_all = getattr(torch, "_foreach_zero_", None)
+
+
 def _raw_stream(stream=None, device=None) -> int:
     """The HIP stream of `stream`, or the current one of `device` (None: of
-    the current device).  The current stream's handle alone: making torch's
-    Stream object of it takes 2.7 us, twice per call, and the handle 0.1."""
+    the current device)."""
     if stream is not None:
         return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if device is None else device.index)
+    if _current_raw is None or (device is not None and device.type != "cuda"):
+        return torch.cuda.current_stream(device).cuda_stream  # (raises on other devices)
+    return _current_raw(torch.cuda.current_device() if device is None else device.index)
+
+
+def _zero(tensors) -> None:
+    """Clear device tensors, by one launch where torch can."""
+    if _zero_all is not None:
+        _zero_all(tensors)
+    else:
+        for t in tensors:
+            t.zero_()
 
 
 def _stream(stream=None):
@@ -327,7 +343,7 @@ def acrl_score_pi_mu(h, w, hq, hq_scales, wq, wq_scales, mu_scaling: int, token_
             if out_slot is not None or n_slots != n_rows or (unscored and k.endswith(unscored)):
                 clear.append(out[k])
     if clear:
-        torch._foreach_zero_(clear)
+        _zero(clear)
     desc = ScoreDesc(n_rows=n_rows, d=d, V=V, h=_ptr(h), w=_ptr(w), hq=_ptr(hq),
                      hq_scales=_ptr(hq_scales), wq=_ptr(wq), wq_scales=_ptr(wq_scales),
                      mu_scaling=mu_scaling, inv_temperature=float(inv_temperature),
