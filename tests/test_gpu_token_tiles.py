@@ -73,6 +73,35 @@ def test_workspace_grows_with_rows():
             last = nb.value
 
 
+@pytest.mark.parametrize("scaling", [oracle.PER_TENSOR, oracle.PER_ROW, oracle.MX32])
+def test_unpacked_workspace_grows_with_rows(scaling):
+    """The same where the call packs W and Wq itself from some row count on."""
+    from paper_2607_24062_amd import acrl
+    L = acrl.lib()
+    nb = ctypes.c_size_t()
+    for d, V in ((128, 100), (2048, 151936), (4096, 32003)):
+        last = 0
+        for n in sorted(set(list(range(0, 40000, 97)) + [e + k for e in (3072, 8192, 12288, 16384) for k in (-1, 0, 1, 256)])):
+            assert L.acrl_score_workspace_size(n, d, V, scaling, ctypes.byref(nb)) == 0
+            assert nb.value >= last, (d, V, n)
+            last = nb.value
+
+
+@pytest.mark.parametrize("chunk", [0, 256, 1000, 4096])
+@pytest.mark.parametrize("d,V", [(128, 100), (256, 1000), (256, 20000), (1024, 30000), (2048, 151936), (4096, 151936)])
+def test_backward_workspace_grows_with_rows(d, V, chunk):
+    """The backward's likewise: K slices sized by the rows and (small heads) by the head, W packed above 4 d rows."""
+    from paper_2607_24062_amd import acrl
+    L = acrl.lib()
+    nb = ctypes.c_size_t()
+    last = 0
+    lines = [e + k for e in (256, 4096, 4 * d, 12288, 16384, 32768) for k in (-1, 0, 1, 256)]
+    for n in sorted(set(list(range(0, 600)) + list(range(600, 40000, 97)) + lines)):
+        assert L.acrl_backward_workspace_size(n, d, V, chunk, ctypes.byref(nb)) == 0
+        assert nb.value >= last, n
+        last = nb.value
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("scaling", [oracle.PER_TENSOR, oracle.PER_ROW, oracle.MX32])
 @pytest.mark.parametrize("T,V", [(1, 100), (130, 300), (700, 1000), (3072, 300), (3073, 300), (8192, 300), (8193, 300),
