@@ -16,10 +16,11 @@
 //    BF16: v_mfma_f32_32x32x16_bf16.  FP8: v_mfma_f32_32x32x64_f8f6f4.
 //    MXFP8: v_mfma_scale_f32_32x32x64_f8f6f4 with per-lane E8M0 block scales.
 //  * K is streamed in 64-byte chunks per row (32 bf16 or 64 fp8 values) from
-//    packed tile images straight into LDS (buffer_load ... lds), in a ring of
-//    5 stages (4 for the per-row and MX scorers) with one barrier per chunk
-//    and an XOR swizzle of the 16-byte columns so that fragment reads are
-//    bank-conflict free.
+//    packed tile images (W, where the caller packed none and the rows are few,
+//    from its rows) straight into LDS (buffer_load ... lds), in a ring of 5
+//    stages (4 for the per-row and MX scorers; 6 to 8 with the narrow tiles)
+//    with one barrier per chunk and an XOR swizzle of the 16-byte columns so
+//    that fragment reads are bank-conflict free.
 //  * Each workgroup sweeps a strip of vocabulary tiles for one token tile and
 //    keeps a running (max, sum, entropy-sum) state per token in registers:
 //    the [rows, V] logits never reach memory.  Online update, in log2 units
@@ -331,7 +332,7 @@ void score_kernel(ScoreParams p) {
   constexpr int NS = Pipe<MODE, TT>::kStages;
   constexpr int kStageBytes = Pipe<MODE, TT>::kStageBytes;
   // accumulators held in VGPRs (the MFMA's VGPR form): the 8-wave per-row FP8
-  // kernels and the 8-wave passes of the full-vocabulary measures (12 instead
+  // kernels and the 8-wave passes of the full-vocabulary measures (packed: 12 instead
   // of 112 bytes spilled per lane in the persistent per-row scorer, mu 1.5-7 %
   // faster, and 12 instead of 104 in pi's measures pass, the measures 6 ms
   // cheaper at d = 4096; the plain 256-token BF16 and per-tensor FP8 scorers
@@ -368,7 +369,7 @@ void score_kernel(ScoreParams p) {
   const int vt_end = min(vt_begin + p.tiles_per_strip, p.n_vtiles);
   const int n_iter = (vt_end - vt_begin) * n_kc;
 
-  // ---- per-lane tokens: column r32 of each of the wave's 4 token blocks
+  // ---- per-lane tokens: column r32 of each of the wave's JT token blocks
   int tok[4], id[4];
   float c2[4], cz[4];
   float gl2[4], gc[4];  // backward: lse (log2 units) and coef / tau of the lane's tokens
@@ -889,8 +890,8 @@ void score_kernel(ScoreParams p) {
   // past V and tokens past n_rows or with coef 0 store 0 (the select also
   // drops a non-finite p of such a row).  Stores go through buffer resources of
   // one 16 KiB image block each: scalar block addresses and six lane offsets in
-  // all, where 64-bit lane addresses filled the registers (228 VGPRs, and
-  // spills with two waves per SIMD; 150 now).
+  // all, where 64-bit lane addresses filled the registers (228 VGPRs at one
+  // wave per SIMD, and spills at two; 125 beside the 128 accumulators at two now).
   auto grad_epilogue = [&](int tile) {
     const int vw = tile * kTileV + wv * 128;  // first vocabulary row of this wave
     const bool odd = (lane & 1) != 0;
@@ -1249,7 +1250,10 @@ constexpr int waves_for() {
 // d = 4096 and 5120, 3 % at d = 2048; per-tensor FP8 mu 2.5 %, MX 1 %,
 // per-row FP8 mu 6 % at d = 2048 and 1.5 % at d = 4096), except the per-row
 // FP8 pass that stores its logits (the unit loop spills it to 104 bytes per
-// lane, and the measures call ran no faster).  p.queue must point at
+// lane, and the measures call of 81083 rows ran no faster; where the XCDs'
+// shares of raster blocks differ it takes rounds of units more than plan_score
+// counts: 2900 rows at V = 151936 are 34 blocks, 5 rounds on two XCDs and 4 on
+// the others, 1.24 ms).  p.queue must point at
 // kXcds * kQueueStride ints of workspace, cleared here.  The backward's
 // plain products run persistent too (8 waves, VGPR accumulators: the q8b
 // backward 502 -> 490 ms, of which ~1 ms from the persistent grid), and so
