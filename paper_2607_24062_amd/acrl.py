@@ -195,9 +195,10 @@ def _raw_stream(stream=None, device=None) -> int:
     the current device)."""
     if stream is not None:
         return stream.cuda_stream
-    if _current_raw is None or (device is not None and device.type != "cuda"):
+    index = torch.cuda.current_device() if device is None else device.index
+    if _current_raw is None or index is None:
         return torch.cuda.current_stream(device).cuda_stream  # (raises on other devices)
-    return _current_raw(torch.cuda.current_device() if device is None else device.index)
+    return _current_raw(index)
 
 
 def _zero(tensors) -> None:
