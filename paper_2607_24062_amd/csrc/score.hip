@@ -374,7 +374,7 @@ void score_kernel(ScoreParams p) {
   float c2[4], cz[4];
   float gl2[4], gc[4];  // backward: lse (log2 units) and coef / tau of the lane's tokens
   float M[4], S[4], U[4];
-  float bk[4], bz[4];  // sampling: best Gumbel key of the lane and its logit
+  float bk[4], bnear[4], bz[4];  // sampling: best Gumbel key of the lane, the least that may round to it, its logit
   int bi[4];           //           and vocabulary row
 #pragma unroll
   for (int j = 0; j < JT; ++j) {
@@ -390,7 +390,7 @@ void score_kernel(ScoreParams p) {
       gc[j] = cf * p.inv_temp;
       gl2[j] = cf != 0.0f ? p.g_lse[slot] * kLog2e : 0.0f;
     }
-    bk[j] = -INFINITY;
+    bk[j] = bnear[j] = -INFINITY;
     bz[j] = 0.0f;
     bi[j] = 0;
     float ct = p.inv_temp;
@@ -665,7 +665,8 @@ void score_kernel(ScoreParams p) {
           for (int w = 4; w >= 1; w >>= 1)
 #pragma unroll
             for (int i = 0; i < w; ++i) mx[i] = fmaxf(mx[i], mx[i + w]);
-          const float Mn = fmaxf(M[j], mx[0] * c2[j]);
+          const float bm = mx[0] * c2[j];  // the block's maximum
+          const float Mn = fmaxf(M[j], bm);
           const float dM = M[j] - Mn;
           const float al = fast_exp2(dM);
           U[j] = al * fmaf(dM, S[j], U[j]);
@@ -744,18 +745,16 @@ void score_kernel(ScoreParams p) {
             }
             const float u = ((float)(wk >> 9) + 0.5f) * 0x1p-23f;
             const float gum = -__builtin_amdgcn_logf(-__builtin_amdgcn_logf(u));
-            // (the rounding: of exponents up to 2^7, and of M)
-            if (M[j] + __builtin_amdgcn_logf(sh[0]) + gum > bk[j] - fmaf(fabsf(M[j]), 0x1p-20f, 1e-3f)) {
+            if (M[j] + __builtin_amdgcn_logf(sh[0]) + gum > bnear[j]) {
               // the block's row: the first whose cumulative weight exceeds
               // u' times the block's total (in row order), else its last row
-              // of nonzero weight; weights 2^(y - bm), bm the block's maximum
+              // of nonzero weight; weights 2^(y - bm)
               const float up = ((float)(wp >> 9) + 0.5f) * 0x1p-23f;
-              auto valid = [&](int i) { return !kTail || (float)(16 * b + i) < nv; };
-              float bm = kInitMax;
-#pragma unroll
-              for (int i = 0; i < 16; ++i) bm = valid(i) ? fmaxf(bm, v[i] * c2[j]) : bm;
               // two passes over the weights (recomputed: fewer live registers)
-              auto weight = [&](int i) { return valid(i) ? fast_exp2(fmaf(v[i], c2[j], -bm)) : 0.0f; };
+              auto weight = [&](int i) {
+                const float e = fast_exp2(fmaf(v[i], c2[j], -bm));
+                return !kTail || (float)(16 * b + i) < nv ? e : 0.0f;
+              };
               float tot = 0.0f;
 #pragma unroll
               for (int i = 0; i < 16; ++i) tot += weight(i);
@@ -780,6 +779,9 @@ void score_kernel(ScoreParams p) {
               }
               if (key > bk[j]) {
                 bk[j] = key;
+                // (the rounding: of exponents up to 2^7, and of M, which is
+                // within 32 of the best key or far above it)
+                bnear[j] = key - fmaf(fabsf(key), 0x1p-20f, 1e-3f);
                 bz[j] = zsel * cz[j];
                 bi[j] = v0 + 32 * b + 8 * (isel >> 2) + 4 * g + (isel & 3);
               }
