@@ -481,9 +481,9 @@ acrl_status acrl_surrogate(const acrl_surrogate_desc* desc, void* stream);
  * Requirements: n_rows >= 0; d > 0, d % 128 == 0; 0 < V < 2^23;
  * (V rounded up to 256) * d / 8 < 2^32; token_chunk >= 0 (0 = 16384; rounded
  * up to a multiple of 256; at most 2^23); workspace of
- * acrl_backward_workspace_size() bytes (W^T, packed W above min(4 d, 16384)
- * rows, one chunk of H, H^T and two bf16 copies of its dZ: about
- * 4 V d + 4 c d + 4 c V bytes for a chunk of c rows; plus at most 512 MiB of
+ * acrl_backward_workspace_size() bytes (W^T, packed W above 4 d rows (4096 at
+ * least, 16384 at most), one chunk of H, H^T and two bf16 copies of its dZ:
+ * about 4 V d + 4 c d + 4 c V bytes for a chunk of c rows; plus at most 512 MiB of
  * fp32 partial products where a product of few output tiles is split along K,
  * and the products' work-queue counters, cleared by the call).              */
 typedef struct acrl_backward_desc {

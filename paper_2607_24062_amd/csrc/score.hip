@@ -1748,11 +1748,12 @@ Raster raster_blocks(int n_ttiles, int n_strips) {
 //  - MXFP8, d = 4096: mu 1.33 / 1.19 at 2048 rows, 2.35 / 2.33 at 4096, draws 1.42 /
 //    1.30 and 2.53 / 2.55, 4.79 / 4.97 at 8192; d = 2048: draws 0.82 / 0.78, 1.49 /
 //    1.53 and 2.78 / 3.00;
-//  - the backward, whose copy is W's alone and whose line rises with d (up to
-//    4 d rows, 16384 at most): d = 4096 4.55 / 4.10 at 1024 rows, 39.6 / 38.9 at
+//  - the backward, whose copy is W's alone and whose line rises with d (4 d
+//    rows, but 4096 at least and 16384 at most): d = 4096 4.55 / 4.10 at 1024 rows, 39.6 / 38.9 at
 //    12288, 53.1 / 51.8 at 16384; d = 2048 7.16 / 7.08 at 4096, 13.42 / 13.40 at 8192,
 //    26.5 / 26.6 at 16384; d = 1024, V = 30000 0.827 / 0.804 at 4096, 0.987 / 0.994 at
-//    5000, 2.25 / 2.28 at 12000.
+//    5000, 2.25 / 2.28 at 12000; d = 256, V = 151936 0.667 / 0.653 at 1100, 1.54 / 1.52
+//    at 4096.
 // (The row offset is a 24-bit product.)
 constexpr int64_t kReadInPlaceRows = 12288, kMeasuresInPlaceRows = 8192, kMxInPlaceRows = 3072;
 static bool read_in_place(int64_t n_rows, int64_t d, int64_t most) {
@@ -2115,7 +2116,7 @@ BackwardPlan plan_backward(int64_t n_rows, int64_t d, int64_t V, int64_t chunk) 
     off += align_up(bytes, 256);
     return o;
   };
-  pl.pack_w = !read_in_place(n_rows, d, std::min<int64_t>(4 * d, 16384));
+  pl.pack_w = !read_in_place(n_rows, d, std::clamp<int64_t>(4 * d, 4096, 16384));
   pl.off_w = take(pl.pack_w ? vrows * 2 * (size_t)d : 0);  // W, rows = vocabulary, K = d (many rows: else read in place)
   pl.off_wt = take(drows * vrows * 2);                     // W^T, rows = d, K = vocabulary
   pl.off_h = take(crows * 2 * (size_t)d);                  // H chunk, rows = tokens, K = d
