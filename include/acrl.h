@@ -156,7 +156,7 @@ acrl_status acrl_fp8_encode(const float* x, int64_t n, int rounding, void* q, vo
  * given, becomes nonzero; the flag is never cleared by the library).
  * The workspace holds a tiled copy of h and hq and of the E8M0 scales of Wq and
  * hq, for calls of many rows also of W and Wq (both above 12288 rows, 8192 with
- * the measures below, an MXFP8 Wq above 3072; then about
+ * the measures below, an MXFP8 Wq of more than 8 MB above 4096; then about
  * (3 + 1/32) (V + n_rows) d bytes; with fewer rows W and Wq are read where
  * they lie), besides the per-strip partial states and the work-queue counters
  * of the persistent launches (cleared by the call itself); with

@@ -1746,8 +1746,10 @@ Raster raster_blocks(int n_ttiles, int n_strips) {
 //  - the measures (their passes spill more in place), d = 2048: 4096 rows
 //    4.31 / 4.10, 8192 8.03 / 7.98, 12288 11.93 / 12.01;
 //  - MXFP8, d = 4096: mu 1.33 / 1.19 at 2048 rows, 2.35 / 2.33 at 4096, draws 1.42 /
-//    1.30 and 2.53 / 2.55, 4.79 / 4.97 at 8192; d = 2048: draws 0.82 / 0.78, 1.49 /
-//    1.53 and 2.78 / 3.00;
+//    1.30 and 2.53 / 2.53, 4.76 / 4.97 at 8192; d = 2048: draws 0.82 / 0.78, 1.47 /
+//    1.48 and 2.80 / 2.93; d = 1024: 0.84 / 0.83 at 3100, 0.97 / 0.96 at 4096, 1.84 /
+//    1.89 at 8192; a Wq of up to 8 MB has cache left for the half lines and is
+//    worth no launch: d = 1024, V = 2048 0.053 / 0.050 at 8192;
 //  - the backward, whose copy is W's alone and whose line rises with d (4 d
 //    rows, but 4096 at least and 16384 at most): d = 4096 4.55 / 4.10 at 1024 rows, 39.6 / 38.9 at
 //    12288, 53.1 / 51.8 at 16384; d = 2048 7.16 / 7.08 at 4096, 13.42 / 13.40 at 8192,
@@ -1755,7 +1757,8 @@ Raster raster_blocks(int n_ttiles, int n_strips) {
 //    5000, 2.25 / 2.28 at 12000; d = 256, V = 151936 0.667 / 0.653 at 1100, 1.54 / 1.52
 //    at 4096.
 // (The row offset is a 24-bit product.)
-constexpr int64_t kReadInPlaceRows = 12288, kMeasuresInPlaceRows = 8192, kMxInPlaceRows = 3072;
+constexpr int64_t kReadInPlaceRows = 12288, kMeasuresInPlaceRows = 8192, kMxInPlaceRows = 4096;
+constexpr int64_t kMxSmallHead = (int64_t)8 << 20;
 static bool read_in_place(int64_t n_rows, int64_t d, int64_t most) {
   return n_rows <= most && 2 * d < ((int64_t)1 << 24);
 }
@@ -1849,7 +1852,7 @@ ScorePlan plan_score(int64_t n_rows, int64_t d, int64_t V, bool mx, int64_t div_
   // rows are too many to read W and Wq in place
   const int64_t in_place = div_rows > 0 ? kMeasuresInPlaceRows : kReadInPlaceRows;
   pl.pack_w = !prepacked && !read_in_place(n_rows, d, in_place);
-  pl.pack_wq = !prepacked && !read_in_place(n_rows, d, mx ? kMxInPlaceRows : in_place);
+  pl.pack_wq = !prepacked && !read_in_place(n_rows, d, mx && V * d > kMxSmallHead ? kMxInPlaceRows : in_place);
   const size_t vrows = (size_t)pl.n_vtiles * kTileV, trows = (size_t)pl.n_ptiles * kTileT;
   const size_t pack_bytes[4] = {vrows * 2 * (size_t)d, trows * 2 * (size_t)d, vrows * (size_t)d, trows * (size_t)d};
   for (int q = 0; q < 4; ++q) {

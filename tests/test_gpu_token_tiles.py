@@ -81,7 +81,7 @@ def test_unpacked_workspace_grows_with_rows(scaling):
     nb = ctypes.c_size_t()
     for d, V in ((128, 100), (2048, 151936), (4096, 32003)):
         last = 0
-        for n in sorted(set(list(range(0, 40000, 97)) + [e + k for e in (3072, 8192, 12288, 16384) for k in (-1, 0, 1, 256)])):
+        for n in sorted(set(list(range(0, 40000, 97)) + [e + k for e in (4096, 8192, 12288, 16384) for k in (-1, 0, 1, 256)])):
             assert L.acrl_score_workspace_size(n, d, V, scaling, ctypes.byref(nb)) == 0
             assert nb.value >= last, (d, V, n)
             last = nb.value
@@ -104,11 +104,11 @@ def test_backward_workspace_grows_with_rows(d, V, chunk):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("scaling", [oracle.PER_TENSOR, oracle.PER_ROW, oracle.MX32])
-@pytest.mark.parametrize("T,V", [(1, 100), (130, 300), (700, 1000), (3072, 300), (3073, 300), (8192, 300), (8193, 300),
-                                 (12288, 300), (12289, 300)])
+@pytest.mark.parametrize("T,V", [(1, 100), (130, 300), (700, 1000), (8192, 300), (8193, 300),
+                                 (12288, 300), (12289, 300), (4096, 33000), (4097, 33000)])
 def test_weights_read_in_place_equal_packed(scaling, T, V):
     """W and Wq read where they lie (up to 12288 rows, 8192 with the measures, an
-    MXFP8 Wq up to 3072), packed by the call (above) and packed by the caller:
+    MXFP8 Wq of more than 8 MB up to 4096), packed by the call (above) and packed by the caller:
     the same bits everywhere."""
     torch, dev = torch_dev()
     from paper_2607_24062_amd import acrl
@@ -149,10 +149,10 @@ def test_backward_weights_read_in_place_equal_packed():
 
 def test_workspace_holds_the_packed_weights_above_the_lines():
     """An unpacked call's workspace has room for a packed W above 12288 rows, 8192 with the measures, and for a
-    packed Wq likewise, of MXFP8 above 3072 (host arithmetic only)."""
+    packed Wq likewise, of MXFP8 above 4096 where it has more than 8 MB (host arithmetic only)."""
     from paper_2607_24062_amd import acrl
     L = acrl.lib()
-    V, d = 151936, 2048
+    V, d = 4097, 2048
     buf = ctypes.c_void_p(256)
 
     def extra(n, scaling, div):  # bytes beyond the call's that brings packed weights, in images of Wq (2 of W)
@@ -167,5 +167,7 @@ def test_workspace_holds_the_packed_weights_above_the_lines():
     for scaling in (acrl.SCALE_PER_TENSOR, acrl.SCALE_PER_ROW):
         assert [extra(n, scaling, False) for n in (1, 4096, 12288, 12289)] == [0, 0, 0, 3]
         assert [extra(n, scaling, True) for n in (1, 8192, 8193)] == [0, 0, 3]
-    assert [extra(n, acrl.SCALE_MX32, False) for n in (1, 3072, 3073, 12288, 12289)] == [0, 0, 1, 1, 3]
-    assert [extra(n, acrl.SCALE_MX32, True) for n in (1, 3072, 3073, 8192, 8193)] == [0, 0, 1, 1, 3]
+    assert [extra(n, acrl.SCALE_MX32, False) for n in (1, 4096, 4097, 12288, 12289)] == [0, 0, 1, 1, 3]
+    assert [extra(n, acrl.SCALE_MX32, True) for n in (1, 4096, 4097, 8192, 8193)] == [0, 0, 1, 1, 3]
+    V = 4096
+    assert [extra(n, acrl.SCALE_MX32, False) for n in (4097, 12288, 12289)] == [0, 0, 3]
